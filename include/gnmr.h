@@ -218,7 +218,9 @@ gnmr_status gnmr_wgrad_sumsq(const void* dy, const void* x, void* dw, int64_t to
  * or x, or tile_sumsq (operands may be shared between problems: the seven
  * projections read three inputs).  Nothing is launched if a check fails.
  * The overwriting and the accumulating problems of a batch run as separate
- * launches (one kernel instance per kind), in that order. */
+ * launches (one kernel instance per kind), in that order.  Launches of few
+ * tiles run in smaller ones and add a launch for the tile sums; the results
+ * have the same bits however a problem is batched. */
 typedef struct {
   const void* dy;        /* device [tokens][out_features] bf16 */
   const void* x;         /* device [tokens][in_features] bf16  */

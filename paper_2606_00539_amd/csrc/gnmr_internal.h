@@ -120,7 +120,7 @@ constexpr int kWgBK = 64;
 constexpr int kWgThreads = 256;
 constexpr int kWgGroupRows = 8;
 
-constexpr int kWgMaxBatch = 16;   // problems per launch (passed by value)
+constexpr int kWgMaxBatch = 32;   // problems per launch (passed by value)
 
 struct WgProblem {
   const uint16_t* dy;  // [K][M]
@@ -129,13 +129,13 @@ struct WgProblem {
   float* tile_ss;      // [tiles_m * tiles_n]
   int64_t K;
   int32_t M, N, tiles_m, tiles_n;
-  int32_t tile_begin;  // first tile of this problem in the launch's tile order
   int32_t accumulate;  // 1: add the product to the stored dw
 };
 
 struct WgBatch {
   int32_t num;
   int32_t total_tiles;
+  int32_t tile_begin[kWgMaxBatch];  // each problem's first tile in the launch's tile order
   WgProblem p[kWgMaxBatch];
 };
 

@@ -718,14 +718,10 @@ gnmr_status gnmr_wgrad_sumsq_batched(const gnmr_wgrad_problem* problems, int32_t
       P.K = q.tokens;
       P.M = q.out_features;
       P.N = q.in_features;
-      P.tiles_m = (q.out_features + gnmr::kWgBM - 1) / gnmr::kWgBM;
-      P.tiles_n = (q.in_features + gnmr::kWgBN - 1) / gnmr::kWgBN;
-      P.tile_begin = int32_t(tiles);
       P.accumulate = q.accumulate;
       tiles += t;
       ++i;
     }
-    b.total_tiles = int32_t(tiles);
     GNMR_HIP(gnmr::launch_wgrad(b, st));
     base += tiles;
   }

@@ -31,6 +31,16 @@
 // consecutive output columns, 8 contiguous bytes once rounded.  Overwritten
 // tiles that lie wholly inside dw pass through LDS and leave as full rows;
 // the others store each lane's 8 bytes directly.
+//
+// Launches whose 256 tiles would leave most CUs idle run in 128x128 or 64x64
+// tiles instead (tile_edge), and k5_tile_sums then forms the sums of the
+// 256x256 tiles.  Every tile size accumulates over k in the same order, and the
+// squares are added in the same order, so the results have the same bits.
+// The 28 gradients of a 4-layer, d = 256 model at 2,037 tokens (52 tiles of 256):
+// 98 us in 256 tiles (two launches of at most 16 problems), 37 us in 208 tiles
+// of 128 (one launch of at most 32, 26 us, and the sums, 6 us).
+
+#include <type_traits>
 
 #include "gnmr_internal.h"
 
@@ -48,12 +58,23 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 // Buffer resource word 3 for gfx9-family raw (untyped) buffers.
 constexpr int kBufferWord3 = 0x00020000;
-constexpr int kLdsRow = kWgBN + 32;          // row stride 576 B: rows fall 64 B apart in the banks
-constexpr int kStage = kWgBK * kLdsRow;      // elements per operand and stage
-constexpr int kChunks = kWgBK * kWgBN / 8 / kWgThreads;  // 16-byte chunks per lane, operand and stage
 static_assert(kWgBM == kWgBN, "square tiles: one load pattern serves both operands");
-static_assert(kChunks == 8, "load pattern");
 static_assert(kWgBK == 64, "four slots of 16 per K step");
+
+// Geometry of a kT x kT workgroup tile (kT = 256, 128 or 64): four waves, a
+// quarter of the tile each, as kB x kB matrix-core blocks of 32x32.
+template <int kT>
+struct Tile {
+  static constexpr int kB = kT / 64;         // blocks per wave and dimension
+  static constexpr int kW = kT / 2;          // rows and columns of a wave's quarter
+  static constexpr int kVec = kT / 8;        // 16-byte vectors per tile row
+  static constexpr int kRow = kT + 32;       // LDS row stride: rows fall 64 B apart in the banks
+  static constexpr int kStage = kWgBK * kRow;                 // elements per operand and stage
+  static constexpr int kChunks = kWgBK * kVec / kWgThreads;   // 16-byte chunks per lane, operand and stage
+  static constexpr int kPass = kWgThreads / kVec;             // tile rows the workgroup covers at once
+  static constexpr int kAhead = kT == 256 ? 1 : kT == 128 ? 2 : 4;  // K steps in staging registers
+  static constexpr int kSets = kT == 64 ? 4 : 2;                   // fragment register sets
+};
 // sched_group_barrier instruction classes
 constexpr int kSchedMfma = 0x008;
 constexpr int kSchedVmemRead = 0x020;
@@ -77,26 +98,92 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p0, const uint16_t* p1) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// The problem that tile v of the launch belongs to; v becomes its tile there.
+__device__ __forceinline__ int problem_of(const WgBatch& batch, int& v) {
+  int pi = 0, begin = 0;
+#pragma unroll
+  for (int i = 1; i < kWgMaxBatch; ++i) {
+    const int b = batch.tile_begin[i];  // INT32_MAX past the last problem
+    if (v >= b) {
+      pi = i;
+      begin = b;
+    }
+  }
+  v -= begin;
+  return pi;
+}
+
+// A 256x256 (or smaller) bf16 tile of dw at (m0, n0) in LDS: rows of kT
+// elements without padding, chunk c of row r in slot c ^ (r % kVec), so that
+// reads of 32 consecutive rows at one column spread over the banks.  Loaded by
+// direct-to-LDS 16-byte loads, which need no registers: each wavefront
+// instruction fills 1 KiB of consecutive rows.  Rows or columns outside dw
+// read its last row or vector instead (never used).
+template <int kT, int kWaves>
+__device__ __forceinline__ void tile_to_lds(uint16_t* tile, const uint16_t* dw, int m0, int n0,
+                                            int M, int N, int tid) {
+  constexpr int kVec = Tile<kT>::kVec, kRows = 64 / kVec;  // rows per instruction
+  constexpr int kLoads = kT / kRows / kWaves;              // instructions per wave
+  const int row0 = __builtin_amdgcn_readfirstlane(tid >> 6) * kLoads * kRows;
+  const int lane = tid & 63, lrow = lane / kVec;
+#pragma unroll 1
+  for (int q = 0; q < kLoads; ++q) {
+    const int first = row0 + q * kRows, row = first + lrow;
+    const int m = min(m0 + row, M - 1);
+    const int n = min(n0 + 8 * ((lane % kVec) ^ (row & (kVec - 1))), N - 8);
+    __builtin_amdgcn_global_load_lds((const void*)(dw + int64_t(m) * N + n),
+                                     (__attribute__((address_space(3))) void*)(tile + first * kT),
+                                     16, 0, 0);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
+// Address in such a tile of the four elements at (row, col .. col+3).
+template <int kT>
+__device__ __forceinline__ uint16_t* tile_at(uint16_t* tile, int row, int col) {
+  constexpr int kVec = Tile<kT>::kVec;
+  return &tile[row * kT + 8 * ((col >> 3) ^ (row & (kVec - 1))) + (col & 7)];
+}
+
+// Adds the squares of four packed bf16 values to ss, in order.
+__device__ __forceinline__ void add_squares(const u32x2& p, float& ss) {
+  const float q0 = __uint_as_float(p.x << 16), q1 = __uint_as_float(p.x & 0xFFFF0000u),
+              q2 = __uint_as_float(p.y << 16), q3 = __uint_as_float(p.y & 0xFFFF0000u);
+  ss = fmaf(q0, q0, ss);
+  ss = fmaf(q1, q1, ss);
+  ss = fmaf(q2, q2, ss);
+  ss = fmaf(q3, q3, ss);
+}
+
+// The sum over a wave's lanes (a butterfly) to red[wave], for the first four
+// waves of the workgroup.
+__device__ __forceinline__ void wave_sum_to(float ss, float* red, int tid) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) ss += __shfl_xor(ss, d, 64);
+  if ((tid & 63) == 0 && tid < kWgThreads) red[tid >> 6] = ss;
+}
+
 // kAcc: every problem of the batch accumulates into its stored dw (true) or
 // overwrites it (false); a batch of both kinds takes one launch of each.
-template <bool kAcc>
-__global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds[2][2][kStage];  // [stage][x, dy]
-  __shared__ float red[kWgThreads / 64];
+// kT: the tile edge.  256 writes the tile sums itself; the smaller tiles leave
+// them to k5_tile_sums.
+template <bool kAcc, int kT>
+__global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const WgBatch batch) {
+  using G = Tile<kT>;
+  constexpr int kB = G::kB, kW = G::kW, kRow = G::kRow, kChunks = G::kChunks, kPass = G::kPass;
+  constexpr int kAhead = G::kAhead, kSets = G::kSets;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2][2][G::kStage];  // [stage][x, dy]
 
   // Workgroup -> tile: workgroups w, w+8, ... run on one XCD, so give each
   // XCD a contiguous run of the tile order (over all problems of the batch);
   // inside a problem the order walks groups of 8 tile rows column by column,
   // so that the tiles an XCD holds at once share their dy and x panels in
   // its L2.
-  const int G = batch.total_tiles;
+  const int total = batch.total_tiles;
   const int w = blockIdx.x;
-  const int xcd = w % kNumXcd, q = G / kNumXcd, r = G % kNumXcd;
+  const int xcd = w % kNumXcd, q = total / kNumXcd, r = total % kNumXcd;
   int v = xcd * q + (xcd < r ? xcd : r) + w / kNumXcd;
-  int pi = 0;
-  while (pi + 1 < batch.num && v >= batch.p[pi + 1].tile_begin) ++pi;
-  const WgProblem& P = batch.p[pi];
-  v -= P.tile_begin;
+  const WgProblem& P = batch.p[problem_of(batch, v)];
   const uint16_t* __restrict__ dy = P.dy;
   const uint16_t* __restrict__ x = P.x;
   uint16_t* __restrict__ dw = P.dw;
@@ -107,13 +194,13 @@ __global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
   const int rows = tiles_m - first_m < kWgGroupRows ? tiles_m - first_m : kWgGroupRows;
   const int tm = first_m + (v % per_group) % rows;
   const int tn = (v % per_group) / rows;
-  const int m0 = tm * kWgBM, n0 = tn * kWgBN;
+  const int m0 = tm * kT, n0 = tn * kT;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;  // this wave's 128x128 quarter
+  const int wm = wave >> 1, wn = wave & 1;  // this wave's quarter of the tile
 
-  // Global -> LDS: lane tid moves 16-byte chunk (row tid/32 + 8c, column
-  // 8*(tid%32)) of each operand tile, c = 0..7, with buffer loads whose
+  // Global -> LDS: lane tid moves 16-byte chunk (row tid/kVec + kPass*c, column
+  // 8*(tid%kVec)) of each operand tile, c < kChunks, with buffer loads whose
   // resource covers the rows of one K step: rows past K and columns past M
   // or N (whose offset is pushed past the resource) read as zero in
   // hardware, so every load is issued unconditionally (M, N multiples of 8:
@@ -121,11 +208,11 @@ __global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
   // resource: their loads read zeros without touching memory, and the
   // buffers they fill are never read, which keeps the loop body free of
   // branches.
-  const int lrow = tid >> 5, lcol = (tid & 31) * 8;
+  const int lrow = tid / G::kVec, lcol = (tid % G::kVec) * 8;
   const uint32_t kOut = 0x80000000u;  // beyond any resource of this kernel
   const uint32_t xo = n0 + lcol < N ? uint32_t((lrow * N + n0 + lcol) * 2) : kOut;
   const uint32_t yo = m0 + lcol < M ? uint32_t((lrow * M + m0 + lcol) * 2) : kOut;
-  u32x4 rx[kChunks], ry[kChunks];
+  u32x4 rx[kAhead][kChunks], ry[kAhead][kChunks];
   __amdgpu_buffer_rsrc_t xr, yr;
   auto rsrc = [&](int64_t k0) {
     const int64_t kb = k0 < K ? k0 : 0;
@@ -133,20 +220,22 @@ __global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
     xr = __builtin_amdgcn_make_buffer_rsrc((void*)(x + kb * N), 0, rws * N * 2, kBufferWord3);
     yr = __builtin_amdgcn_make_buffer_rsrc((void*)(dy + kb * M), 0, rws * M * 2, kBufferWord3);
   };
-  auto gload = [&](int h) {  // chunks 4h .. 4h+3 of both operands
+  auto gload = [&](int a, int h) {  // half h of both operands' chunks
 #pragma unroll
-    for (int c = 4 * h; c < 4 * h + 4; ++c) {
-      rx[c] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, xo + uint32_t(c * 16 * N), 0, 0));
-      ry[c] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(yr, yo + uint32_t(c * 16 * M), 0, 0));
+    for (int c = kChunks / 2 * h; c < kChunks / 2 * (h + 1); ++c) {
+      rx[a][c] = __builtin_bit_cast(
+          u32x4,
+          __builtin_amdgcn_raw_buffer_load_b128(xr, xo + uint32_t(c * 2 * kPass * N), 0, 0));
+      ry[a][c] = __builtin_bit_cast(
+          u32x4,
+          __builtin_amdgcn_raw_buffer_load_b128(yr, yo + uint32_t(c * 2 * kPass * M), 0, 0));
     }
   };
-  auto lstore = [&](int buf, int h) {
+  auto lstore = [&](int buf, int a, int h) {
 #pragma unroll
-    for (int c = 4 * h; c < 4 * h + 4; ++c) {
-      *(u32x4*)&lds[buf][0][(lrow + 8 * c) * kLdsRow + lcol] = rx[c];
-      *(u32x4*)&lds[buf][1][(lrow + 8 * c) * kLdsRow + lcol] = ry[c];
+    for (int c = kChunks / 2 * h; c < kChunks / 2 * (h + 1); ++c) {
+      *(u32x4*)&lds[buf][0][(lrow + kPass * c) * kRow + lcol] = rx[a][c];
+      *(u32x4*)&lds[buf][1][(lrow + kPass * c) * kRow + lcol] = ry[a][c];
     }
   };
 
@@ -157,196 +246,235 @@ __global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
   // the two reads h = 0, 1: the same k order for both operands.
   const int f_row = 8 * (lane >> 5) + ((lane & 15) >> 2);
   const int f_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  bf16x8 fx[2][4], fy[2][4];  // [register set][block]
+  bf16x8 fx[kSets][kB], fy[kSets][kB];  // [register set][block]
   auto rfrag = [&](int set, int buf, int kk) {
-    const uint16_t* lx = &lds[buf][0][f_row * kLdsRow + wn * 128 + f_col];
-    const uint16_t* ly = &lds[buf][1][f_row * kLdsRow + wm * 128 + f_col];
+    const uint16_t* lx = &lds[buf][0][f_row * kRow + wn * kW + f_col];
+    const uint16_t* ly = &lds[buf][1][f_row * kRow + wm * kW + f_col];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int o = kk * 16 * kLdsRow + 32 * b;
-      fx[set][b] = frag(lx + o, lx + o + 4 * kLdsRow);
-      fy[set][b] = frag(ly + o, ly + o + 4 * kLdsRow);
+    for (int b = 0; b < kB; ++b) {
+      const int o = kk * 16 * kRow + 32 * b;
+      fx[set][b] = frag(lx + o, lx + o + 4 * kRow);
+      fy[set][b] = frag(ly + o, ly + o + 4 * kRow);
     }
   };
 
-  f32x16 acc[4][4];
+  f32x16 acc[kB][kB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < kB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < kB; ++j) acc[i][j] = f32x16{};
   auto mfma = [&](int set) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kB; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < kB; ++j)
         acc[i][j] =
             __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[set][j], fy[set][i], acc[i][j], 0, 0, 0);
   };
-  // Instruction order inside a slot (scheduling hints only): each
-  // matrix-core instruction is followed by two fragment reads for the next
-  // slot, then, in slots 0 and 1, by one LDS store and one global load.
-  auto order_reads = [] {
+  const int64_t nk = (K + kWgBK - 1) / kWgBK;  // 0 steps for an empty batch: dw = 0
+  if constexpr (kT >= 128) {
+    // Instruction order inside a slot (scheduling hints only): each
+    // matrix-core instruction is followed by two fragment reads for the next
+    // slot and, in slots 0 and 1, by one LDS store and one global load (the
+    // 256 tile has matrix-core instructions enough to give these their own).
+    auto order = [](auto stores) {
+      constexpr bool kStores = decltype(stores)::value;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
-    }
-  };
-  auto order_stores = [] {
+      for (int i = 0; i < 2 * kB; ++i) {
+        if constexpr (kT == 128) {
+          if (i % 2 == 0) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+          if constexpr (kStores) {
+            __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
+          }
+        } else {
+          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+        }
+      }
+      if constexpr (kT == 256) {
+        if constexpr (kStores) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
-    }
-  };
+          for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
+          }
+        } else {
+          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8, 0);
+        }
+      }
+    };
+    const std::true_type with_stores;
+    const std::false_type without_stores;
 
-  // 0 steps for an empty batch: dw = 0.  Prologue: step 0 in buffer 0,
-  // step 1 in the staging registers, the first slot's fragments read.
-  const int64_t nk = (K + kWgBK - 1) / kWgBK;
-  rsrc(0);
-  gload(0);
-  gload(1);
-  lstore(0, 0);
-  lstore(0, 1);
-  rsrc(kWgBK);
-  gload(0);
-  gload(1);
-  __syncthreads();
-  rfrag(0, 0, 0);
-  for (int64_t s = 0; s < nk; ++s) {
-    const int buf = int(s & 1);
-    // slot 0: stage half of step s+1, load half of step s+2
-    rfrag(1, buf, 1);
-    lstore(buf ^ 1, 0);
-    rsrc((s + 2) * kWgBK);
-    gload(0);
-    mfma(0);
-    order_reads();
-    order_stores();
-    // slot 1: the other halves
-    rfrag(0, buf, 2);
-    lstore(buf ^ 1, 1);
-    gload(1);
-    mfma(1);
-    order_reads();
-    order_stores();
-    // slot 2
-    rfrag(1, buf, 3);
-    mfma(0);
-    order_reads();
-    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8, 0);
-    // slot 3: every wave has stored its part of step s+1 and read its last
-    // fragments of buffer s%2 (the barrier waits for both), so buffer
-    // (s+1)%2 is complete and buffer s%2 free for step s+2
-    __builtin_amdgcn_sched_barrier(0);
+    // Prologue: step 0 in buffer 0, steps 1 .. kAhead in the staging
+    // registers (step s in set s % kAhead), the first slot's fragments read.
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      rsrc(int64_t(a) * kWgBK);
+      gload(a, 0);
+      gload(a, 1);
+    }
+    lstore(0, 0, 0);
+    lstore(0, 0, 1);
+    rsrc(int64_t(kAhead) * kWgBK);
+    gload(0, 0);
+    gload(0, 1);
     __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
-    rfrag(0, buf ^ 1, 0);
-    mfma(1);
-    order_reads();
-    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8, 0);
+    rfrag(0, 0, 0);
+    for (int64_t s0 = 0; s0 < nk; s0 += kAhead) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int64_t s = s0 + u;
+        if (u > 0 && s >= nk) break;
+        const int buf = kAhead > 1 ? u & 1 : int(s & 1), a = (u + 1) % kAhead;
+        // slot 0: stage half of step s+1, load half of step s+1+kAhead
+        rfrag(1, buf, 1);
+        lstore(buf ^ 1, a, 0);
+        rsrc((s + 1 + kAhead) * kWgBK);
+        gload(a, 0);
+        mfma(0);
+        order(with_stores);
+        // slot 1: the other halves
+        rfrag(0, buf, 2);
+        lstore(buf ^ 1, a, 1);
+        gload(a, 1);
+        mfma(1);
+        order(with_stores);
+        // slot 2
+        rfrag(1, buf, 3);
+        mfma(0);
+        order(without_stores);
+        // slot 3: every wave has stored its part of step s+1 and read its last
+        // fragments of buffer s%2 (the barrier waits for both), so buffer
+        // (s+1)%2 is complete and buffer s%2 free for step s+2
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        rfrag(0, buf ^ 1, 0);
+        mfma(1);
+        order(without_stores);
+      }
+    }
+  } else {
+    // The 64 tile: a step has four matrix-core instructions per wave, less
+    // than the latency of one LDS read, so it reads all its fragments at once
+    // behind its one barrier.
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      rsrc(int64_t(a) * kWgBK);
+      gload(a, 0);
+      gload(a, 1);
+    }
+    lstore(0, 0, 0);
+    lstore(0, 0, 1);
+    rsrc(int64_t(kAhead) * kWgBK);
+    gload(0, 0);
+    gload(0, 1);
+    for (int64_t s0 = 0; s0 < nk; s0 += kAhead) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int64_t s = s0 + u;
+        if (s >= nk) break;
+        const int buf = u & 1, a = (u + 1) % kAhead;
+        // Buffer s%2 is complete, and every wave has its fragments of step
+        // s-1, so buffer (s+1)%2 is free.
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < kSets; ++kk) rfrag(kk, buf, kk);
+        lstore(buf ^ 1, a, 0);
+        lstore(buf ^ 1, a, 1);
+        rsrc((s + 1 + kAhead) * kWgBK);
+        gload(a, 0);
+        gload(a, 1);
+#pragma unroll
+        for (int kk = 0; kk < kSets; ++kk) mfma(kk);
+      }
+    }
   }
 
   // Epilogue: accumulator register r of block (i, j) holds output row
-  // m = m0 + 128*wm + 32*i + lane%32 and column
-  // n = n0 + 128*wn + 32*j + 8*(r/4) + 4*(lane/32) + r%4.  When the problem
+  // m = m0 + kW*wm + 32*i + lane%32 and column
+  // n = n0 + kW*wn + 32*j + 8*(r/4) + 4*(lane/32) + r%4.  When the problem
   // accumulates, the stored gradient is first widened and added in fp32 (one
-  // rounding), then the sum is rounded to bf16 once.
+  // rounding), then the sum is rounded to bf16 once.  The stored tile comes
+  // through the LDS buffers, which are free once the loop is done.
+  // Squares are summed along a lane's row of blocks i first, then over i; the
+  // rows' sums wait in LDS past the tile (no register is free for them).
   float ss = 0.0f;
-  const int m_lane = m0 + wm * 128 + (lane & 31);
-  const int n_lane = n0 + wn * 128 + 4 * (lane >> 5);
-  // Accumulating: the stored tile is first copied into the LDS buffers (free
-  // once the loop is done) by direct-to-LDS 16-byte loads, which need no
-  // registers: each wavefront instruction fills two rows of 512 B, and chunk
-  // c of row r sits in slot c ^ (r % 32) of its row, so that the epilogue's
-  // reads of 32 consecutive rows at one column spread over the banks.  Loads
-  // of rows or columns outside dw read dw[0] instead (never used).
-  uint16_t* const old_tile = &lds[0][0][0];
-  static_assert(kWgBM * kWgBN <= 2 * 2 * kStage, "the stored tile fits in the LDS buffers");
-  auto stage_old = [&]() {
-    __syncthreads();  // every wave is done with the operand buffers
-    const int row_in_pair = lane >> 5, slot = lane & 31;
-#pragma unroll 1
-    for (int q = 0; q < kWgBM / 2 / 4; ++q) {  // 32 row pairs per wave
-      const int row = (wave * (kWgBM / 8) + q) * 2 + row_in_pair;
-      const int m = m0 + row, n = n0 + 8 * (slot ^ (row & 31));
-      const uint16_t* src = (m < M && n < N) ? dw + int64_t(m) * N + n : dw;
-      __builtin_amdgcn_global_load_lds(
-          (const void*)src,
-          (__attribute__((address_space(3))) void*)(old_tile + (row & ~1) * kWgBN), 16, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  };
-  auto old_pair = [&](int m, int n) {  // the stored values at (m, n .. n+3)
-    const int row = m - m0, c = (n - n0) >> 3, w = (n - n0) & 7;
-    return *(const u32x2*)&old_tile[row * kWgBN + 8 * (c ^ (row & 31)) + w];
-  };
+  const int m_lane = m0 + wm * kW + (lane & 31);
+  const int n_lane = n0 + wn * kW + 4 * (lane >> 5);
+  uint16_t* const tile = &lds[0][0][0];
+  static_assert(kT * kT <= 2 * 2 * G::kStage, "the stored tile fits in the LDS buffers");
   // Rounds one group of four accumulator values (row m, columns n .. n+3)
   // and adds their squares to ss in a fixed order; returns them packed.
   auto round_group = [&](int i, int j, int g, int m, int n) {
     float v0 = acc[i][j][4 * g + 0], v1 = acc[i][j][4 * g + 1], v2 = acc[i][j][4 * g + 2],
           v3 = acc[i][j][4 * g + 3];
     if constexpr (kAcc) {
-      const u32x2 old = old_pair(m, n);
+      const u32x2 old = *(const u32x2*)tile_at<kT>(tile, m - m0, n - n0);
       v0 += bf16_val(old.x & 0xFFFFu);
       v1 += bf16_val(old.x >> 16);
       v2 += bf16_val(old.y & 0xFFFFu);
       v3 += bf16_val(old.y >> 16);
     }
-    const uint32_t p01 = pack_bf16(v0, v1), p23 = pack_bf16(v2, v3);
-    const float q0 = __uint_as_float(p01 << 16), q1 = __uint_as_float(p01 & 0xFFFF0000u),
-                q2 = __uint_as_float(p23 << 16), q3 = __uint_as_float(p23 & 0xFFFF0000u);
-    ss = fmaf(q0, q0, ss);
-    ss = fmaf(q1, q1, ss);
-    ss = fmaf(q2, q2, ss);
-    ss = fmaf(q3, q3, ss);
-    return u32x2{p01, p23};
+    const u32x2 p{pack_bf16(v0, v1), pack_bf16(v2, v3)};
+    if constexpr (kT == 256) add_squares(p, ss);
+    return p;
   };
-  auto epilogue = [&]() {
-    if constexpr (kAcc) stage_old();
-    if (!kAcc && m0 + kWgBM <= M && n0 + kWgBN <= N) {
-      // Overwriting a tile wholly inside dw (uniform): the rounded tile goes
-      // to the free LDS buffers first, in the swizzled layout of the stored
-      // tile, then leaves in full rows: each wavefront store covers two whole
-      // 512-byte rows, where a lane's own accumulator layout would touch 32
-      // rows with 16 bytes each.  (Accumulating, the same staging spills
-      // registers and measured no faster, so those tiles store directly.)
-      __syncthreads();  // every wave is done with the operand buffers
+  float* const row_sums = (float*)(tile + kT * kT);
+  static_assert(kT != 256 || kT * kT * 2 + kB * kWgThreads * 4 <= 2 * 2 * G::kStage * 2, "LDS");
+  auto end_row = [&](int i) {
+    if constexpr (kT == 256) {
+      row_sums[i * kWgThreads + int(threadIdx.x)] = ss;
+      ss = 0.0f;
+    }
+  };
+  __syncthreads();  // every wave is done with the operand buffers
+  if constexpr (kAcc) {
+    tile_to_lds<kT, 4>(tile, dw, m0, n0, M, N, tid);
+    __syncthreads();
+  }
+  if (!kAcc && m0 + kT <= M && n0 + kT <= N) {
+    // Overwriting a tile wholly inside dw (uniform): the rounded tile goes
+    // to the free LDS buffers first, in the swizzled layout of the stored
+    // tile, then leaves in full rows: each wavefront store covers whole rows
+    // (1 KiB of them), where a lane's own accumulator layout would touch 32
+    // rows with 16 bytes each.  (Accumulating, the same staging spills
+    // registers in the 256 tile and measured no faster, so those tiles store
+    // directly.)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kB; ++i) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          // one block at a time: its conversions and LDS accesses stay next
-          // to their use, within the registers the accumulators leave free
-          __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < kB; ++j) {
+        // one block at a time: its conversions and LDS accesses stay next
+        // to their use, within the registers the accumulators leave free
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int m = m_lane + 32 * i, n = n_lane + 32 * j + 8 * g;
-            const u32x2 v = round_group(i, j, g, m, n);
-            const int row = m - m0, c = (n - n0) >> 3, w = (n - n0) & 7;
-            *(u32x2*)&old_tile[row * kWgBN + 8 * (c ^ (row & 31)) + w] = v;
-          }
+        for (int g = 0; g < 4; ++g) {
+          const int m = m_lane + 32 * i, n = n_lane + 32 * j + 8 * g;
+          *(u32x2*)tile_at<kT>(tile, m - m0, n - n0) = round_group(i, j, g, m, n);
         }
       }
-      __syncthreads();
-      const int c = tid & 31;
-      int row = tid >> 5;
-      uint16_t* out = dw + int64_t(m0 + row) * N + n0 + 8 * c;
-#pragma unroll 4
-      for (int p = 0; p < kWgBM * kWgBN / 8 / kWgThreads; ++p) {
-        *(g_vec4*)out = *(const u32x4*)&old_tile[row * kWgBN + 8 * (c ^ (row & 31))];
-        row += kWgThreads / 32;
-        out += int64_t(kWgThreads / 32) * N;
-      }
-      return;
+      end_row(i);
     }
+    __syncthreads();
+    int row = lrow;
+    uint16_t* out = dw + int64_t(m0 + row) * N + n0 + lcol;
+#pragma unroll 4
+    for (int p = 0; p < kT / kPass; ++p) {
+      *(g_vec4*)out = *(const u32x4*)tile_at<kT>(tile, row, lcol);
+      row += kPass;
+      out += int64_t(kPass) * N;
+    }
+  } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kB; ++i) {
       const int m = m_lane + 32 * i;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < kB; ++j) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -354,14 +482,53 @@ __global__ __launch_bounds__(kWgThreads) void k5_wgrad(const WgBatch batch) {
           if (m < M && n < N) *(g_vec2*)(dw + int64_t(m) * N + n) = round_group(i, j, g, m, n);
         }
       }
+      end_row(i);
     }
-  };
-  epilogue();
+  }
+  if constexpr (kT == 256) {
+    __shared__ float red[kWgThreads / 64];
+    ss = row_sums[tid];
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) ss += __shfl_xor(ss, d, 64);
-  if (lane == 0) red[wave] = ss;
+    for (int i = 1; i < kB; ++i) ss += row_sums[i * kWgThreads + tid];
+    wave_sum_to(ss, red, tid);
+    __syncthreads();
+    if (tid == 0) P.tile_ss[tm * tiles_n + tn] = ((red[0] + red[1]) + red[2]) + red[3];
+  }
+}
+
+constexpr int kSumsThreads = 1024;
+
+// The tile sums of problems whose GEMM ran in smaller tiles: one workgroup per
+// 256x256 tile reads the stored tile back (at most 128 KiB, just written).
+// Sixteen waves, each with the part of one 256-tile wave that its row of
+// blocks i makes, add the squares in that kernel's order, so a tile sum has
+// the same bits on either path.
+__global__ __launch_bounds__(kSumsThreads) void k5_tile_sums(const WgBatch batch) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[256 * 256];
+  __shared__ float part[4][256];  // [block row i][lane of the 256-tile kernel]
+  __shared__ float red[kWgThreads / 64];
+  int v = blockIdx.x;
+  const WgProblem& P = batch.p[problem_of(batch, v)];
+  const int M = P.M, N = P.N, m0 = v / P.tiles_n * 256, n0 = v % P.tiles_n * 256;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  tile_to_lds<256, kSumsThreads / 64>(tile, P.dw, m0, n0, M, N, tid);
   __syncthreads();
-  if (tid == 0) P.tile_ss[tm * tiles_n + tn] = ((red[0] + red[1]) + red[2]) + red[3];
+  const int i = wave >> 2, quarter = wave & 3;
+  const int row = 128 * (quarter >> 1) + 32 * i + (lane & 31);
+  const int col0 = 128 * (quarter & 1) + 4 * (lane >> 5);
+  float ss = 0.0f;
+#pragma unroll
+  for (int jg = 0; jg < 16; ++jg) {
+    const int col = col0 + 8 * jg;
+    if (m0 + row < M && n0 + col < N) add_squares(*(const u32x2*)tile_at<256>(tile, row, col), ss);
+  }
+  part[i][64 * quarter + lane] = ss;
+  __syncthreads();
+  if (tid < kWgThreads)
+    ss = ((part[0][tid] + part[1][tid]) + part[2][tid]) + part[3][tid];
+  wave_sum_to(ss, red, tid);
+  __syncthreads();
+  if (tid == 0) P.tile_ss[v] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 }  // namespace
@@ -370,24 +537,79 @@ int64_t wgrad_tiles(int32_t M, int32_t N) {
   return int64_t((M + kWgBM - 1) / kWgBM) * int64_t((N + kWgBN - 1) / kWgBN);
 }
 
+namespace {
+
+// `batch`'s problems of one kind (accumulate == acc), cut into kT tiles.
+template <int kT>
+WgBatch tiled(const WgBatch& batch, int acc) {
+  WgBatch b{};
+  for (int32_t& t : b.tile_begin) t = INT32_MAX;
+  for (int i = 0; i < batch.num; ++i) {
+    if (batch.p[i].accumulate != acc) continue;
+    WgProblem P = batch.p[i];
+    P.tiles_m = (P.M + kT - 1) / kT;
+    P.tiles_n = (P.N + kT - 1) / kT;
+    b.tile_begin[b.num] = b.total_tiles;
+    b.total_tiles += P.tiles_m * P.tiles_n;
+    b.p[b.num++] = P;
+  }
+  return b;
+}
+
+template <int kT>
+void launch_tiled(const WgBatch& batch, int acc, hipStream_t s) {
+  const WgBatch b = tiled<kT>(batch, acc);
+  if (acc)
+    hipLaunchKernelGGL((k5_wgrad<true, kT>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0, s,
+                       b);
+  else
+    hipLaunchKernelGGL((k5_wgrad<false, kT>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0,
+                       s, b);
+}
+
+// The tile edge for one launch.  A 256 tile does the most work per LDS byte
+// and writes its own sum, but takes 8.5 us plus 1.1 us per K step of 64
+// however few of the 256 CUs have one; the smaller tiles add the k5_tile_sums
+// launch (about 6 us) and spread the same steps over 4 or 16 times the
+// workgroups.  Measured on square problems, call to call, 256 / 128 / 64 tile:
+//   tokens 4096:  G = 1: 77 / 40 / 28 us    G = 16: 78 / 44 / 31
+//                 G = 64: 79 / 46 / 65      G = 121: 80 / 75 / 114
+//                 G = 144: 81 / 106 / 130   (G: number of 256 tiles)
+//   tokens 1024:  G = 1: 25 / 18 / 14       G = 64: 27 / 23 / 26
+//                 G = 100: 27 / 27 / 36
+//   tokens 256:   G = 16: 12.3 / 12.5 / 11  G = 64: 13 / 16 / 18
+// So: the 64 tile while every CU gets at most one and there are 4 steps to
+// share; the 128 tile while every CU gets at most one and the steps outweigh
+// the second launch (4 plus one per 64 tiles more), or at most two and 32
+// steps; otherwise the 256 tile.
+int tile_edge(const WgBatch& batch, int acc) {
+  const WgBatch b = tiled<64>(batch, acc);
+  const int64_t n64 = b.total_tiles, n128 = tiled<128>(batch, acc).total_tiles;
+  int64_t steps = 0;
+  for (int i = 0; i < b.num; ++i)
+    steps = b.p[i].K > steps * kWgBK ? (b.p[i].K + kWgBK - 1) / kWgBK : steps;
+  if (n64 <= 256 && steps >= 4) return 64;
+  if (n128 <= 256 && steps >= 4 + n128 / 64) return 128;
+  if (n128 <= 512 && steps >= 32) return 128;
+  return 256;
+}
+
+}  // namespace
+
 hipError_t launch_wgrad(const WgBatch& batch, hipStream_t s) {
   // one launch per epilogue kind: the problems that overwrite dw, then those
   // that accumulate into it, each launch with its own tile order
   for (const int acc : {0, 1}) {
-    WgBatch b{};
-    for (int i = 0; i < batch.num; ++i) {
-      if ((batch.p[i].accumulate != 0) != (acc != 0)) continue;
-      WgProblem P = batch.p[i];
-      P.tile_begin = b.total_tiles;
-      b.total_tiles += P.tiles_m * P.tiles_n;
-      b.p[b.num++] = P;
-    }
+    const WgBatch b = tiled<256>(batch, acc);
     if (b.total_tiles == 0) continue;
-    if (acc)
-      hipLaunchKernelGGL(k5_wgrad<true>, dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0, s, b);
-    else
-      hipLaunchKernelGGL(k5_wgrad<false>, dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0, s,
-                         b);
+    const int t = tile_edge(batch, acc);
+    if (t == 256) {
+      launch_tiled<256>(batch, acc, s);
+    } else {
+      if (t == 128) launch_tiled<128>(batch, acc, s);
+      else launch_tiled<64>(batch, acc, s);
+      hipLaunchKernelGGL(k5_tile_sums, dim3(unsigned(b.total_tiles)), dim3(kSumsThreads), 0, s, b);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -1,0 +1,89 @@
+"""K5's tile sizes (256, and 128 or 64 where 256 tiles would leave compute
+units idle): the same problem through each of them gives the same bits, and
+those lie within the oracle's bound.  The tile of a launch follows from its
+problems, so a problem gets the 256 tile in a batch with a large filler and
+the 128 tile with a medium one."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from gpu_util import require_gpu
+from oracle import wgrad as W
+from synth import wgrad as SW
+
+pytestmark = pytest.mark.gpu
+
+SS_RTOL = 264 * 2.0 ** -24
+
+
+def to_dev(torch, bits):
+    return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).to("cuda")
+
+
+def launch(torch, problems, filler):
+    """dw and tile sums of the problems (dy, x, old dw, accumulate), batched
+    with a filler problem of filler x filler features and 320 tokens when
+    filler > 0."""
+    from paper_2606_00539_amd import gnmr_wgrad_num_tiles, gnmr_wgrad_sumsq_batched
+
+    probs = [(to_dev(torch, dy), to_dev(torch, x), to_dev(torch, old), dy.shape[0], dy.shape[1],
+              x.shape[1], acc) for dy, x, old, acc in problems]
+    if filler:
+        z = torch.zeros((320, filler), dtype=torch.int16, device="cuda")
+        for acc in sorted({p[6] for p in probs}):
+            out = torch.zeros((filler, filler), dtype=torch.int16, device="cuda")
+            probs.append((z, z, out, 320, filler, filler, acc))
+    off = np.concatenate([[0], np.cumsum([gnmr_wgrad_num_tiles(p[4], p[5]) for p in probs])])
+    ss = torch.full((int(off[-1]),), float("nan"), dtype=torch.float32, device="cuda")
+    gnmr_wgrad_sumsq_batched(probs, ss)
+    torch.cuda.synchronize()
+    ss = ss.cpu().numpy()
+    return [(p[2].cpu().numpy().view(np.uint16), ss[off[i]:off[i + 1]])
+            for i, p in enumerate(probs[:len(problems)])]
+
+
+# tile edges of 64, 128 and 256 and one vector past them; tokens around the K
+# step of 64 and the staging rings of two and four steps
+@pytest.mark.parametrize("M,N,T", [(8, 8, 256), (64, 72, 257), (72, 64, 319), (128, 136, 320),
+                                   (136, 264, 321), (256, 328, 449), (264, 520, 512),
+                                   (520, 248, 577)])
+def test_every_tile_size_gives_the_same_bits(M, N, T):
+    torch = require_gpu()
+    print(f"wgrad tiles M={M} N={N} T={T}", flush=True)
+    dy, x = SW.operands(3, 1, M + N, tokens=T, out_f=M, in_f=N)
+    old = W.bf16_rne(np.random.default_rng(M * N).standard_normal((M, N)) * 0.02)
+    problems = [(dy, x, old, 0), (dy, x, old, 1)]
+    small = launch(torch, problems, 0)          # 64: at most 256 workgroups
+    medium = launch(torch, problems, 1280)      # 128: over 256 of 64, under 256 of 128
+    large = launch(torch, problems, 3072)       # 256
+    for (acc, a, b, c) in zip((0, 1), small, medium, large):
+        for name, other in (("128", b), ("256", c)):
+            assert np.array_equal(a[0], other[0]), f"accumulate={acc}: dw of the {name} tile"
+            assert np.array_equal(a[1], other[1]), f"accumulate={acc}: sums of the {name} tile"
+        if acc:
+            exact = W.wgrad_accumulate_exact(old, dy, x)
+            bound = W.error_bound_accumulate(old, dy, x, exact)
+        else:
+            exact = W.wgrad_exact(dy, x)
+            bound = W.error_bound(dy, x, exact)
+        assert np.all(np.abs(W.widen_bf16(a[0]) - exact) <= bound), f"accumulate={acc}"
+        np.testing.assert_allclose(a[1], W.tile_sumsq(a[0]), rtol=SS_RTOL, atol=0)
+
+
+def test_more_problems_than_one_launch_holds():
+    """35 problems (a launch holds 32) of differing sizes and both kinds: every
+    dw the oracle's bit for bit on integer operands, tile sums at the
+    concatenated offsets."""
+    torch = require_gpu()
+    shapes = [(8 * (1 + i % 5), 8 * (1 + i % 7), 40 + i) for i in range(35)]
+    problems = []
+    for i, (M, N, T) in enumerate(shapes):
+        dy, x = SW.small_integer_operands(50 + i, T, M, N)
+        old = W.bf16_rne(np.random.default_rng(i).integers(-8, 9, (M, N)).astype(np.float64))
+        problems.append((dy, x, old, i % 2))
+    for i, ((dy, x, old, acc), (dw, ss)) in enumerate(zip(problems, launch(torch, problems, 0))):
+        want = W.bf16_rne(W.wgrad_accumulate_exact(old, dy, x) if acc else W.wgrad_exact(dy, x))
+        assert np.array_equal(dw, want), f"problem {i}"
+        np.testing.assert_allclose(ss, W.tile_sumsq(want), rtol=SS_RTOL, atol=0,
+                                   err_msg=f"problem {i}")
