@@ -86,16 +86,21 @@ struct SelectArgs {
   gnmr_stats* stats;
 };
 
-// K4 (actuator): up to kK4Vpt 16-byte vectors per lane; one wavefront per
-// row of at most kK4WaveCols bf16 features, one workgroup per longer row of
-// at most kK4MaxCols.
+// K4 (actuator): rows by width, each class with its own lanes per row and
+// 16-byte vectors per lane (see k4_actuator.hip).
 constexpr int kK4Block = 256;
-constexpr int kK4Vpt = 8;
-constexpr int kK4WaveCols = 64 * kK4Vpt * 8;
-constexpr int kK4MaxCols = kK4Block * kK4Vpt * 8;
+constexpr int kK4Classes = 12;
+constexpr int kK4MaxCols = 16384;
+int k4_class(int cols);
+// Inputs of up to this many bytes are read with ordinary loads.  Between 34 MB
+// (4096 x 4096: 12.4 us against 14.6 non-temporal) and 134 MB (16384 x 4096:
+// 52.8 against 51.3); input and output together then fit the memory-side cache.
+constexpr int64_t kK4CachedBytes = int64_t(64) << 20;
+// Rows of up to this many features count as narrow in the limits on rows per
+// call: 4 * kK4MaxWorkgroups of them and kK4MaxWorkgroups longer ones.
+constexpr int kK4NarrowCols = 4096;
 // A launch's grid holds fewer than 2^32 work items: at most this many
-// workgroups of kK4Block lanes, i.e. this many wide rows or four times as many
-// narrow ones per launch.
+// workgroups of kK4Block lanes.
 constexpr int64_t kK4MaxWorkgroups = int64_t(UINT32_MAX) / kK4Block;
 
 struct ActSeg {
@@ -141,13 +146,12 @@ struct WgBatch {
 
 int64_t wgrad_tiles(int32_t M, int32_t N);
 hipError_t launch_wgrad(const WgBatch& batch, hipStream_t s);
-// Rows [0, num_narrow) of `items` have at most kK4WaveCols features (one
-// wavefront each), rows [num_narrow, num_rows) more (one workgroup each).
-hipError_t launch_actuate(const RowItem* items, int64_t num_narrow, int64_t num_rows,
+// Rows [class_off[c], class_off[c + 1]) of `items` are of row class c; `bytes`
+// is the bf16 input of all rows.
+hipError_t launch_actuate(const RowItem* items, const int64_t* class_off, int64_t bytes,
                           const ActSeg* segs, const uint8_t* mask, int fmt_low, int fmt_rec,
                           hipStream_t s);
-// One [rows][sg.cols] matrix, no row table: rows <= 4 * UINT32_MAX when
-// sg.cols <= kK4WaveCols, else rows <= UINT32_MAX (one workgroup each).
+// One [rows][sg.cols] matrix, no row table.
 hipError_t launch_actuate_matrix(const ActSeg& sg, int64_t rows, const uint8_t* mask,
                                  int fmt_low, int fmt_rec, hipStream_t s);
 hipError_t launch_sumsq(const Item* items, int64_t num_items, const char* const* seg_base,

@@ -1025,7 +1025,7 @@ struct gnmr_actuator {
   int device = 0;
   int32_t num_units = 0;
   int64_t rows = 0;
-  int64_t narrow_rows = 0;  // rows [0, narrow_rows) of the list take one wavefront each
+  int64_t class_off[gnmr::kK4Classes + 1] = {};  // first row of each row class in the list
   int64_t bytes = 0;
   void* arena = nullptr;
   gnmr::RowItem* d_items = nullptr;
@@ -1060,9 +1060,9 @@ gnmr_status gnmr_actuator_create(gnmr_actuator** out, const gnmr_act_segment* se
   {
     int64_t narrow_rows = 0;
     for (int64_t k = 0; k < num_segments; ++k)
-      if (segs[k].cols <= gnmr::kK4WaveCols) narrow_rows += segs[k].rows;
+      if (segs[k].cols <= gnmr::kK4NarrowCols) narrow_rows += segs[k].rows;
     if (narrow_rows > 4 * gnmr::kK4MaxWorkgroups || rows - narrow_rows > gnmr::kK4MaxWorkgroups)
-      return fail(GNMR_E_INVALID, "too many rows for one launch: at most " +
+      return fail(GNMR_E_INVALID, "too many rows for one call: at most " +
                                       std::to_string(4 * gnmr::kK4MaxWorkgroups) +
                                       " rows of up to 4096 features and " +
                                       std::to_string(gnmr::kK4MaxWorkgroups) + " longer rows");
@@ -1085,26 +1085,26 @@ gnmr_status gnmr_actuator_create(gnmr_actuator** out, const gnmr_act_segment* se
       return fail(GNMR_E_INVALID, "activation segment " + std::to_string(k) +
                                       ": out overlaps another segment's input or output");
   }
-  // Row list: the rows that one wavefront handles first, then the longer ones.
+  // Row list: by row class, within a class in segment order.
   std::vector<gnmr::RowItem> items;
   items.reserve(size_t(rows));
   std::vector<gnmr::ActSeg> dsegs(static_cast<size_t>(num_segments));
   for (int64_t k = 0; k < num_segments; ++k)
     dsegs[size_t(k)] = gnmr::ActSeg{static_cast<const char*>(segs[k].in),
                                     static_cast<char*>(segs[k].out), segs[k].cols, segs[k].unit};
-  for (int pass = 0; pass < 2; ++pass)
+  int64_t class_off[gnmr::kK4Classes + 1] = {};
+  for (int c = 0; c < gnmr::kK4Classes; ++c) {
     for (int64_t k = 0; k < num_segments; ++k)
-      if ((segs[k].cols <= gnmr::kK4WaveCols) == (pass == 0))
+      if (gnmr::k4_class(segs[k].cols) == c)
         for (int64_t r = 0; r < segs[k].rows; ++r)
           items.push_back(gnmr::RowItem{int32_t(k), int32_t(r)});
-  int64_t narrow = 0;
-  for (int64_t k = 0; k < num_segments; ++k)
-    if (segs[k].cols <= gnmr::kK4WaveCols) narrow += segs[k].rows;
+    class_off[c + 1] = int64_t(items.size());
+  }
   gnmr_actuator* a = new (std::nothrow) gnmr_actuator;
   if (a == nullptr) return fail(GNMR_E_NOMEM, "host allocation failed");
   a->num_units = num_units;
   a->rows = rows;
-  a->narrow_rows = narrow;
+  std::copy(class_off, class_off + gnmr::kK4Classes + 1, a->class_off);
   a->bytes = bytes;
   const size_t o_items = 0;
   const size_t o_segs = align_up(std::max<size_t>(items.size() * sizeof(gnmr::RowItem), 1), 256);
@@ -1145,7 +1145,7 @@ gnmr_status gnmr_actuate(gnmr_actuator* act, const uint8_t* d_mask, int32_t fmt_
     return fail(GNMR_E_INVALID, "unknown format");
   DeviceGuard g(act->device);
   if (!g.ok) return fail(GNMR_E_HIP, "cannot select the actuator's device");
-  GNMR_HIP(gnmr::launch_actuate(act->d_items, act->narrow_rows, act->rows, act->d_segs, d_mask,
+  GNMR_HIP(gnmr::launch_actuate(act->d_items, act->class_off, act->bytes, act->d_segs, d_mask,
                                 fmt_low, fmt_recovery, static_cast<hipStream_t>(stream)));
   return GNMR_OK;
 }
@@ -1156,8 +1156,8 @@ gnmr_status gnmr_actuate_matrix(const void* in, void* out, int64_t rows, int32_t
   if (rows < 0 || rows > INT32_MAX) return fail(GNMR_E_INVALID, "rows must be in [0, 2^31)");
   if (cols < 8 || cols > gnmr::kK4MaxCols || cols % 8 != 0)
     return fail(GNMR_E_INVALID, "cols must be a multiple of 8 in [8, 16384]");
-  if (rows > (cols <= gnmr::kK4WaveCols ? 4 : 1) * gnmr::kK4MaxWorkgroups)
-    return fail(GNMR_E_INVALID, "too many rows for one launch: at most " +
+  if (rows > (cols <= gnmr::kK4NarrowCols ? 4 : 1) * gnmr::kK4MaxWorkgroups)
+    return fail(GNMR_E_INVALID, "too many rows for one call: at most " +
                                     std::to_string(4 * gnmr::kK4MaxWorkgroups) +
                                     " rows of up to 4096 features or " +
                                     std::to_string(gnmr::kK4MaxWorkgroups) + " longer rows");

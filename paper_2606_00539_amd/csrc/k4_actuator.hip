@@ -5,16 +5,31 @@
 // and rescaled; Sec. 5.1 / App. E.4: token-wise low-bit saved activations;
 // Sec. 5.3 / App. E.3: the INT8 low-cost path).
 //
-// One wavefront per token row of up to 4096 features, one workgroup per
-// longer row (up to 16384), the row held in registers: amax by a
-// max-reduction, one fp32 division each for the scale and its reciprocal,
-// then per element y = x * inv, round to the format (ties to the even
-// significand, saturating), out = bf16_rne(q * s).  A row whose unit takes
-// the BF16 path in place is left untouched without reading it.  The rows come
-// from a table built once over many segments (k4_actuate*), or from one
-// matrix passed by value (k4_matrix*, no table).  Rows are
-// dealt to the eight XCDs in contiguous runs, and both loads and stores are
-// non-temporal: every byte is read and written once.
+// A token row is held in the registers of part of a wavefront (up to 512
+// features), a wavefront (up to 3,072) or a workgroup of 256 or 512 lanes (up
+// to 16,384): amax by a max-reduction, one fp32 division each for the scale and
+// its reciprocal, then per element y = x * inv, round to the format (ties to
+// the even significand, saturating), out = bf16_rne(q * s).  A row whose unit
+// takes the BF16 path in place is left untouched without reading it.  The rows
+// come from a table built once over many segments (k4_actuate), or from one
+// matrix passed by value (k4_matrix, no table).
+//
+// Bound by memory: every byte is read and written once.  The lanes per row and
+// the vectors per lane (for_class) keep few registers idle, so that enough rows
+// are in flight per CU; rows are dealt to the eight XCDs in contiguous runs.
+// Stores are non-temporal.  So are the loads of large sets; up to kK4CachedBytes
+// of input the loads are ordinary ones, since such an input was often written
+// just before and is in the memory-side cache (256 MB), which ordinary loads
+// leave it in.  Measured (read + write; before: one wavefront per row up to
+// 4,096 features and a workgroup above, room for 8 vectors per lane always,
+// non-temporal loads; copy: a plain copy with non-temporal loads and stores):
+//   4096 x 5120    14.8 us (5.7 TB/s)   before 19.5   copy 16.2
+//   4096 x 4096    12.4 us              before 14.1   copy 13.3
+//   2048 x 11008   15.8 us              before 21.1   copy 17.2
+//   4096 x 1024     4.6 us              before  6.0   copy  5.0
+//   16384 x 4096   51.3 us (5.2 TB/s)   before 54.9   copy 50.3   (non-temporal)
+#include <algorithm>
+
 #include "gnmr_internal.h"
 
 namespace gnmr {
@@ -83,58 +98,75 @@ __device__ __forceinline__ void store(g_vec* p, const u32x4& v) {
   __builtin_nontemporal_store(v, p);
 }
 
-// Row `row` of segment sg by LANES lanes (64: a wavefront; kK4Block: the
-// workgroup).  Every lane of the group calls it; `red` is workgroup LDS when
-// LANES > 64.
-template <int LANES>
-__device__ __forceinline__ void actuate_row(const ActSeg sg, int64_t row,
+template <bool kCached>
+__device__ __forceinline__ u32x4 load(const g_cvec* p) {
+  if constexpr (kCached) return *p;
+  else return __builtin_nontemporal_load(p);
+}
+
+// Row `row` of segment sg (none when !valid) by LANES lanes of kVpt vectors
+// each; kUniform: a wavefront's rows are of one unit.  Every lane of the workgroup calls it, and a row of more than 64 lanes
+// has the workgroup to itself; `red` is then LDS of LANES / 64 floats.
+template <int LANES, int kVpt, bool kCached, bool kUniform>
+__device__ __forceinline__ void actuate_row(const ActSeg sg, int64_t row, bool valid,
                                             const uint8_t* __restrict__ mask, int fmt_low,
                                             int fmt_rec, int lane, float* red) {
-  const int fmt = mask[sg.unit] ? fmt_rec : fmt_low;
   const int64_t row_off = row * sg.cols * 2;
-  if (fmt == GNMR_FMT_BF16 && sg.in == sg.out) return;  // BF16 path in place: nothing to do
   const g_cvec* in = (const g_cvec*)(sg.in + row_off);
   g_vec* out = (g_vec*)(sg.out + row_off);
-  const int nvec = sg.cols >> 3;
+  int nvec = valid ? sg.cols >> 3 : 0;
+  // The unit's mask entry is on its way while the row is read; only where the
+  // BF16 path in place may leave the row unread is it waited for first.  The
+  // zero offset is opaque: the compiler would move a wave-uniform entry to a
+  // scalar register, and wait for it, at once.
+  const uint8_t* const entry = mask + sg.unit + __builtin_amdgcn_mbcnt_lo(0u, 0u);
+  const uint8_t on = *entry;
+  if (sg.in == sg.out && (fmt_low == GNMR_FMT_BF16 || fmt_rec == GNMR_FMT_BF16) &&
+      (on ? fmt_rec : fmt_low) == GNMR_FMT_BF16)
+    nvec = 0;
 
-  u32x4 v[kK4Vpt];
+  u32x4 v[kVpt];
 #pragma unroll
-  for (int k = 0; k < kK4Vpt; ++k) {
+  for (int k = 0; k < kVpt; ++k) {
     const int i = lane + k * LANES;
-    v[k] = i < nvec ? __builtin_nontemporal_load(in + i) : u32x4{0u, 0u, 0u, 0u};
+    v[k] = i < nvec ? load<kCached>(in + i) : u32x4{0u, 0u, 0u, 0u};
   }
+  __builtin_amdgcn_sched_barrier(0);
+  int fmt = on ? fmt_rec : fmt_low;
+  if constexpr (kUniform) fmt = __builtin_amdgcn_readfirstlane(fmt);
   if (fmt == GNMR_FMT_BF16) {  // BF16 path out of place: a copy
 #pragma unroll
-    for (int k = 0; k < kK4Vpt; ++k) {
+    for (int k = 0; k < kVpt; ++k) {
       const int i = lane + k * LANES;
       if (i < nvec) store(out + i, v[k]);
     }
-    return;
+    nvec = 0;
   }
 
   // amax over the row (max is exact, so the reduction order is immaterial)
   float m = 0.0f;
 #pragma unroll
-  for (int k = 0; k < kK4Vpt; ++k) {
+  for (int k = 0; k < kVpt; ++k) {
     m = max_abs_pair(v[k].x, m);
     m = max_abs_pair(v[k].y, m);
     m = max_abs_pair(v[k].z, m);
     m = max_abs_pair(v[k].w, m);
   }
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+  for (int d = LANES > 64 ? 32 : LANES / 2; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
   float amax = m;
   if constexpr (LANES > 64) {
-    static_assert(LANES == 4 * 64, "four waves per row");
     if ((lane & 63) == 0) red[lane >> 6] = m;
     __syncthreads();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    amax = red[0];
+#pragma unroll
+    for (int w = 1; w < LANES / 64; ++w) amax = fmaxf(amax, red[w]);
   }
 
   const Format f = format_of(fmt);
   if (amax == 0.0f) {  // an all-zero token stays zero
 #pragma unroll
-    for (int k = 0; k < kK4Vpt; ++k) {
+    for (int k = 0; k < kVpt; ++k) {
       const int i = lane + k * LANES;
       if (i < nvec) store(out + i, u32x4{0u, 0u, 0u, 0u});
     }
@@ -143,7 +175,7 @@ __device__ __forceinline__ void actuate_row(const ActSeg sg, int64_t row,
   const float inv = __fdiv_rn(f.fmax, amax);  // scale into the format's range
   const float s = __fdiv_rn(amax, f.fmax);    // and back
 #pragma unroll
-  for (int k = 0; k < kK4Vpt; ++k) {
+  for (int k = 0; k < kVpt; ++k) {
     const int i = lane + k * LANES;
     if (i < nvec) {
       u32x4 o;
@@ -162,73 +194,148 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t w, uint32_t n) {
   return x * q + (x < r ? x : r) + j;
 }
 
-// At most 80 VGPRs (six waves per SIMD): more rows in flight per CU.
-__global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 8))) void
-k4_actuate_wave(const RowItem* __restrict__ items, uint32_t num_rows,
-                const ActSeg* __restrict__ segs, const uint8_t* __restrict__ mask, int fmt_low,
-                int fmt_rec) {
-  const uint32_t rows_per_wg = kK4Block / 64;
-  const uint32_t r = xcd_order(blockIdx.x, gridDim.x) * rows_per_wg + (threadIdx.x >> 6);
-  if (r >= num_rows) return;
-  const RowItem it = items[r];
-  actuate_row<64>(segs[it.seg], it.row, mask, fmt_low, fmt_rec, int(threadIdx.x & 63), nullptr);
+// Workgroups of 256 lanes, or of one row where that takes more.
+constexpr int block_of(int lanes) { return lanes > kK4Block ? lanes : kK4Block; }
+
+// Waves per SIMD: eight (64 VGPRs) while a lane holds few vectors, six where it
+// holds four or more in a wide row or six: more rows in flight per CU than that
+// cost bandwidth (6103 x 8192: 37.4 us with six, 40.5 with eight; 4066 x 12296:
+// 37.6 and 39.3; but 42207 x 3080, two per lane: 105 and 92).
+#define GNMR_K4_KERNEL                                         \
+  __global__ __launch_bounds__(block_of(LANES)) __attribute__( \
+      (amdgpu_waves_per_eu(waves_of(LANES, kVpt), waves_of(LANES, kVpt))))
+constexpr int waves_of(int lanes, int vpt) { return vpt >= 6 || (vpt >= 4 && lanes > 64) ? 6 : 8; }
+
+// Rows [0, num_rows) of the table.
+template <int LANES, int kVpt, bool kCached>
+GNMR_K4_KERNEL void k4_actuate(const RowItem* __restrict__ items, uint32_t num_rows,
+                               const ActSeg* __restrict__ segs,
+                               const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
+  constexpr int kRows = block_of(LANES) / LANES;  // per workgroup
+  __shared__ float red[block_of(LANES) / 64];
+  const uint32_t sub = kRows > 1 ? threadIdx.x / LANES : 0;
+  const uint32_t r = xcd_order(blockIdx.x, gridDim.x) * kRows + sub;
+  const bool valid = r < num_rows;
+  const RowItem it = items[valid ? r : num_rows - 1];
+  const ActSeg sg = segs[it.seg];
+  __builtin_amdgcn_sched_barrier(0);  // the whole entry at once, not the pointers after the mask
+  actuate_row<LANES, kVpt, kCached, LANES >= 64>(sg, it.row, valid, mask, fmt_low, fmt_rec,
+                                    int(threadIdx.x) % LANES, red);
 }
 
-__global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 8))) void
-k4_actuate(const RowItem* __restrict__ items, const ActSeg* __restrict__ segs,
-           const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
-  __shared__ float red[kK4Block / 64];
-  const RowItem it = items[xcd_order(blockIdx.x, gridDim.x)];
-  actuate_row<kK4Block>(segs[it.seg], it.row, mask, fmt_low, fmt_rec, int(threadIdx.x), red);
+// One matrix without a row table (the segment passed by value).
+template <int LANES, int kVpt, bool kCached>
+GNMR_K4_KERNEL void k4_matrix(const ActSeg sg, uint32_t num_rows,
+                              const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
+  constexpr int kRows = block_of(LANES) / LANES;
+  __shared__ float red[block_of(LANES) / 64];
+  const uint32_t sub = kRows > 1 ? threadIdx.x / LANES : 0;
+  const uint32_t r = xcd_order(blockIdx.x, gridDim.x) * kRows + sub;
+  actuate_row<LANES, kVpt, kCached, true>(sg, r, r < num_rows, mask, fmt_low, fmt_rec,
+                                    int(threadIdx.x) % LANES, red);
 }
 
-// One matrix without a row table (the segment passed by value): rows of at
-// most kK4WaveCols features, four per workgroup, one wavefront each.
-__global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 8))) void
-k4_matrix_wave(const ActSeg sg, int64_t num_rows, const uint8_t* __restrict__ mask, int fmt_low,
-               int fmt_rec) {
-  const int64_t r =
-      int64_t(xcd_order(blockIdx.x, gridDim.x)) * (kK4Block / 64) + (threadIdx.x >> 6);
-  if (r >= num_rows) return;
-  actuate_row<64>(sg, r, mask, fmt_low, fmt_rec, int(threadIdx.x & 63), nullptr);
+// Calls f.template operator()<LANES, kVpt>() for a row class.  The lanes and
+// vectors are the fewest that hold its widest row; where several do, the split
+// that was the fastest or within 3% of it over 512 to 16,384 rows, from the
+// table and as a matrix (us, with its rival):
+//   2048 features, 4,096 rows: 64 x 4  7.9   (128 x 2 7.5, but 11% slower than
+//                                             64 x 4 from the table at 260 MB)
+//   3072, 4,096 rows:          64 x 6 10.2   (128 x 3 9.5, the same)
+//   4096, 2,048 rows:         256 x 2  7.5   (128 x 4 8.3, 64 x 8 8.6)
+//   6144, 1,024 rows:         256 x 3  6.4   (128 x 6 7.0)
+//  11008,   512 rows:         512 x 3  6.0   (256 x 6 6.4; 2,048 rows: 16.1, 15.8)
+//  16384, 1,024 rows:         512 x 4 13.1   (256 x 8 14.1)
+struct RowClass {
+  int lanes, vpt;
+};
+constexpr RowClass kClasses[kK4Classes] = {{8, 2},   {16, 2},  {32, 2},  {64, 2},
+                                           {64, 3},  {64, 4},  {64, 6},  {256, 2},
+                                           {256, 3}, {256, 4}, {512, 3}, {512, 4}};
+static_assert(kClasses[kK4Classes - 1].lanes * kClasses[kK4Classes - 1].vpt * 8 == kK4MaxCols, "");
+
+template <int kClass = 0, typename F>
+void for_class(int cls, const F& f) {
+  if (cls == kClass) f.template operator()<kClasses[kClass].lanes, kClasses[kClass].vpt>();
+  else if constexpr (kClass + 1 < kK4Classes) for_class<kClass + 1>(cls, f);
 }
 
-// One matrix without a row table, rows longer than kK4WaveCols: one
-// workgroup per row.
-__global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 8))) void
-k4_matrix(const ActSeg sg, const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
-  __shared__ float red[kK4Block / 64];
-  actuate_row<kK4Block>(sg, xcd_order(blockIdx.x, gridDim.x), mask, fmt_low, fmt_rec,
-                        int(threadIdx.x), red);
-}
+struct TableLaunch {
+  const RowItem* items;
+  int64_t rows;
+  const ActSeg* segs;
+  const uint8_t* mask;
+  int fmt_low, fmt_rec;
+  bool cached;
+  hipStream_t s;
+  template <int LANES, int kVpt>
+  void operator()() const {
+    constexpr int kBlock = block_of(LANES);
+    constexpr int64_t kRows = kBlock / LANES, kMost = kRows * (int64_t(UINT32_MAX) / kBlock);
+    // a grid holds fewer than 2^32 lanes
+    for (int64_t r = 0; r < rows; r += kMost) {
+      const int64_t n = std::min(rows - r, kMost);
+      const dim3 grid(unsigned((n + kRows - 1) / kRows));
+      if (cached)
+        hipLaunchKernelGGL((k4_actuate<LANES, kVpt, true>), grid, dim3(kBlock), 0, s, items + r,
+                           uint32_t(n), segs, mask, fmt_low, fmt_rec);
+      else
+        hipLaunchKernelGGL((k4_actuate<LANES, kVpt, false>), grid, dim3(kBlock), 0, s, items + r,
+                           uint32_t(n), segs, mask, fmt_low, fmt_rec);
+    }
+  }
+};
+
+struct MatrixLaunch {
+  ActSeg sg;
+  int64_t rows;
+  const uint8_t* mask;
+  int fmt_low, fmt_rec;
+  bool cached;
+  hipStream_t s;
+  template <int LANES, int kVpt>
+  void operator()() const {
+    constexpr int kBlock = block_of(LANES);
+    constexpr int64_t kRows = kBlock / LANES, kMost = kRows * (int64_t(UINT32_MAX) / kBlock);
+    for (int64_t r = 0; r < rows; r += kMost) {
+      const int64_t n = std::min(rows - r, kMost);
+      const dim3 grid(unsigned((n + kRows - 1) / kRows));
+      ActSeg part = sg;
+      part.in += r * sg.cols * 2;
+      part.out += r * sg.cols * 2;
+      if (cached)
+        hipLaunchKernelGGL((k4_matrix<LANES, kVpt, true>), grid, dim3(kBlock), 0, s, part,
+                           uint32_t(n), mask, fmt_low, fmt_rec);
+      else
+        hipLaunchKernelGGL((k4_matrix<LANES, kVpt, false>), grid, dim3(kBlock), 0, s, part,
+                           uint32_t(n), mask, fmt_low, fmt_rec);
+    }
+  }
+};
 
 }  // namespace
 
-hipError_t launch_actuate(const RowItem* items, int64_t num_narrow, int64_t num_rows,
+int k4_class(int cols) {
+  int c = 0;
+  while (cols > kClasses[c].lanes * kClasses[c].vpt * 8) ++c;  // cols <= kK4MaxCols
+  return c;
+}
+
+hipError_t launch_actuate(const RowItem* items, const int64_t* class_off, int64_t bytes,
                           const ActSeg* segs, const uint8_t* mask, int fmt_low, int fmt_rec,
                           hipStream_t s) {
-  const int64_t rows_per_wg = kK4Block / 64;
-  if (num_narrow > 0)
-    hipLaunchKernelGGL(k4_actuate_wave, dim3(unsigned((num_narrow + rows_per_wg - 1) / rows_per_wg)),
-                       dim3(kK4Block), 0, s, items, uint32_t(num_narrow), segs, mask, fmt_low,
-                       fmt_rec);
-  if (num_rows > num_narrow)
-    hipLaunchKernelGGL(k4_actuate, dim3(unsigned(num_rows - num_narrow)), dim3(kK4Block), 0, s,
-                       items + num_narrow, segs, mask, fmt_low, fmt_rec);
+  for (int c = 0; c < kK4Classes; ++c)
+    if (class_off[c + 1] > class_off[c])
+      for_class(c, TableLaunch{items + class_off[c], class_off[c + 1] - class_off[c], segs, mask,
+                               fmt_low, fmt_rec, bytes <= kK4CachedBytes, s});
   return hipGetLastError();
 }
 
 hipError_t launch_actuate_matrix(const ActSeg& sg, int64_t rows, const uint8_t* mask,
                                  int fmt_low, int fmt_rec, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  if (sg.cols <= kK4WaveCols) {
-    const int64_t rows_per_wg = kK4Block / 64;
-    hipLaunchKernelGGL(k4_matrix_wave, dim3(unsigned((rows + rows_per_wg - 1) / rows_per_wg)),
-                       dim3(kK4Block), 0, s, sg, rows, mask, fmt_low, fmt_rec);
-  } else {
-    hipLaunchKernelGGL(k4_matrix, dim3(unsigned(rows)), dim3(kK4Block), 0, s, sg, mask, fmt_low,
-                       fmt_rec);
-  }
+  for_class(k4_class(sg.cols), MatrixLaunch{sg, rows, mask, fmt_low, fmt_rec,
+                                            rows * sg.cols * 2 <= kK4CachedBytes, s});
   return hipGetLastError();
 }
 
