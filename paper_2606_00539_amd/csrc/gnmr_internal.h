@@ -9,37 +9,6 @@
 
 namespace gnmr {
 
-// Step counters accumulated by K2 (integer atomics) and read by K3.
-enum : int {
-  kCntCand = 0,       // |C_t|
-  kCntTrigG = 1,      // recoverable units with GNMR / alpha > 1
-  kCntTrigD = 2,      // recoverable units with Delta-GNMR / beta > 1
-  kCntTrigR = 3,      // recoverable units with R > 1
-  kCntNonFinite = 4,  // units with a non-finite norm
-  kCntRank = 5,       // members of C_t that are ranked for the budget
-  kNumCounters = 8
-};
-
-// K2 spreads its counters and candidate list over this many sets (workgroup
-// w adds to set w % kCounterSets), so that its global atomics do not queue
-// on one address; K3 gathers the sets.
-constexpr int kCounterSets = 64;
-// Entries per set of the candidate list for U units: a set receives at most
-// ceil(workgroups / kCounterSets) workgroups of at most 256 units each.
-inline int64_t cand_list_cap(int64_t num_units) { return num_units / kCounterSets + 512; }
-
-// Per-unit flag bits written by K2 and read by K3.
-enum : uint8_t {
-  kFlagTrigG = 1,      // GNMR / alpha > 1
-  kFlagTrigD = 2,      // Delta-GNMR / beta > 1
-  kFlagNonFinite = 4,  // non-finite norm
-  kFlagTrigR = 8,      // R > 1
-  kFlagRec = 16,       // recoverable
-  kFlagCand = 32,      // member of the candidate pool C_t
-  kFlagKeep = 64       // active without ranking (warm-up; continuing unit under
-                       // the admitted-only budget)
-};
-
 struct UpdateArgs {
   int32_t num_units;
   int32_t window;      // delta
@@ -58,31 +27,31 @@ struct UpdateArgs {
   double* dgnmr;
   double* risk;
   const uint8_t* rec;            // [U]
-  int32_t* lock;                 // [U], Lock after step t-1 (cleared for units outside C_t)
-  uint64_t* keys;                // [U], candidate key or 0
-  uint8_t* flags;
-  uint8_t* mask;                 // [U], A_{t-1} on entry; cleared for units outside C_t
-  int32_t* counters;             // [kCounterSets][kNumCounters], zero on entry
-  int32_t* cand_list;            // [kCounterSets][list_cap]: set j holds counters[j][kCntCand]
-                                 // members of C_t (any order)
-  int64_t list_cap;              // entries per set of cand_list
+  int32_t lock_len;
+  int32_t* lock;                 // [U], in: Lock after step t-1; out: after step t if selected
+  uint8_t* mask;                 // [U], in: A_{t-1}; out: C_t
+  // Members of C_t; K2 workgroup w of n units fills [w * n, ...).
+  uint32_t* pool_rank;           // the upper half of its place in the ranking (larger first), 0:
+                                 // active without ranking (warm-up; continuing unit under the
+                                 // admitted-only budget)
+  int32_t* pool_unit;
+  uint32_t* key_low;             // [U], the lower half of each candidate's place in the ranking
+  uint64_t* wg_counts;           // [workgroups], the packed counts of each workgroup
   double* gsum;                  // [U], sum of GNMR over the static baseline's profiling steps
 };
 
 struct SelectArgs {
-  int32_t num_units;
   int32_t max_o;
-  int32_t lock_len;
-  int32_t warmup;      // warmup_steps (W)
-  int64_t* step;       // steps completed (device); advanced by one at the end of K3
-  const uint8_t* flags;
-  const uint64_t* keys;
-  int32_t* counters;         // from K2, [num_sets][kNumCounters]; reset to zero for the next step
-  const int32_t* cand_list;  // from K2, [num_sets][list_cap]
-  int32_t num_sets;          // kCounterSets (one in the single-workgroup kernel)
-  int64_t list_cap;
-  int32_t* lock;       // in: Lock after step t-1; out: after step t
-  uint8_t* mask;
+  int32_t warmup;              // warmup_steps (W)
+  int64_t* step;               // steps completed (device); advanced by one at the end of K3
+  const uint32_t* pool_rank;   // from K2
+  const int32_t* pool_unit;    // from K2
+  const uint32_t* key_low;     // from K2
+  const uint64_t* wg_counts;   // from K2
+  int32_t num_wgs;             // K2's workgroups,
+  int32_t wg_shift;            // of 1 << wg_shift units each (set by launch_update)
+  int32_t* lock;               // [U], from K2; cleared outside A_t
+  uint8_t* mask;               // [U], C_t from K2; out: A_t
   gnmr_stats* stats;
 };
 
@@ -158,7 +127,7 @@ hipError_t launch_sumsq(const Item* items, int64_t num_items, const char* const*
                         const int32_t* seg_dtype, float* partial, hipStream_t s);
 hipError_t launch_unit_sumsq(const int64_t* unit_item_off, const float* partial,
                              int64_t num_items, int32_t num_units, double* out, hipStream_t s);
-hipError_t launch_update(const UpdateArgs& a, int64_t num_items, hipStream_t s);
+hipError_t launch_update(const UpdateArgs& a, int64_t num_items, SelectArgs* sel, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 // K2 and K3 as one single-workgroup launch: used when the workload is small
 // (at most 1024 units, each summed by one thread, or norms given).

@@ -157,11 +157,11 @@ struct gnmr_ctx {
   double* d_gnmr = nullptr;
   double* d_dgnmr = nullptr;
   double* d_risk = nullptr;
-  uint8_t* d_flags = nullptr;
   uint8_t* d_mask = nullptr;
-  uint64_t* d_keys = nullptr;
-  int32_t* d_counters = nullptr;
-  int32_t* d_cand_list = nullptr;
+  uint32_t* d_pool_rank = nullptr;
+  int32_t* d_pool_unit = nullptr;
+  uint32_t* d_key_low = nullptr;
+  uint64_t* d_wg_counts = nullptr;
   double* d_gsum = nullptr;
   gnmr_stats* d_stats = nullptr;
   int64_t* d_step = nullptr;   // steps completed (advanced by K3)
@@ -320,25 +320,21 @@ gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* 
   u.dgnmr = c->d_dgnmr;
   u.risk = c->d_risk;
   u.rec = c->d_rec;
+  u.lock_len = u.static_set ? 0 : c->lock_len;   // the static baseline uses no locks
   u.lock = c->d_lock;
-  u.keys = c->d_keys;
-  u.flags = c->d_flags;
   u.mask = c->d_mask;
-  u.counters = c->d_counters;
-  u.cand_list = c->d_cand_list;
-  u.list_cap = gnmr::cand_list_cap(c->U);
+  u.pool_rank = c->d_pool_rank;
+  u.pool_unit = c->d_pool_unit;
+  u.key_low = c->d_key_low;
+  u.wg_counts = c->d_wg_counts;
   gnmr::SelectArgs s{};
-  s.num_units = c->U;
   s.max_o = c->max_o;
-  s.lock_len = u.static_set ? 0 : c->lock_len;   // the static baseline uses no locks
   s.warmup = c->warmup_steps;
   s.step = c->d_step;
-  s.flags = c->d_flags;
-  s.keys = c->d_keys;
-  s.counters = c->d_counters;
-  s.cand_list = c->d_cand_list;
-  s.num_sets = gnmr::kCounterSets;
-  s.list_cap = u.list_cap;
+  s.pool_rank = c->d_pool_rank;
+  s.pool_unit = c->d_pool_unit;
+  s.key_low = c->d_key_low;
+  s.wg_counts = c->d_wg_counts;
   s.lock = c->d_lock;
   s.mask = c->d_mask;
   s.stats = c->d_stats;
@@ -350,7 +346,7 @@ gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* 
     if (r == GNMR_OK) r = record(c, 3, st);
     if (r != GNMR_OK) return r;
   } else {
-    GNMR_HIP(gnmr::launch_update(u, num_parts, st));
+    GNMR_HIP(gnmr::launch_update(u, num_parts, &s, st));
     r = record(c, 2, st);
     if (r != GNMR_OK) return r;
     GNMR_HIP(gnmr::launch_select(s, st));
@@ -407,14 +403,6 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   gnmr_status lr = check_layout(segs, U);
   if (lr != GNMR_OK) return lr;
 
-  // K2 workgroups of 1, 4 or 256 units fill counter set w % kCounterSets:
-  // each set's share of the candidate list must fit its capacity
-  for (const int64_t per_wg : {int64_t(1), int64_t(4), int64_t(256)}) {
-    const int64_t wgs = (U + per_wg - 1) / per_wg;
-    if ((wgs + gnmr::kCounterSets - 1) / gnmr::kCounterSets * per_wg > gnmr::cand_list_cap(U))
-      return fail(GNMR_E_INVALID, "candidate list layout does not fit (internal)");
-  }
-
   gnmr_ctx* c = new (std::nothrow) gnmr_ctx;
   if (c == nullptr) return fail(GNMR_E_NOMEM, "host allocation failed");
   c->U = cfg->num_units;
@@ -461,12 +449,12 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   const size_t o_g = take(size_t(U) * sizeof(double));
   const size_t o_d = take(size_t(U) * sizeof(double));
   const size_t o_r = take(size_t(U) * sizeof(double));
-  const size_t o_fl = take(size_t(U));
   const size_t o_mask = take(size_t(U));
-  const size_t o_keys = take(size_t(U) * sizeof(uint64_t));
-  const size_t o_cnt = take(size_t(gnmr::kCounterSets) * gnmr::kNumCounters * sizeof(int32_t));
-  const size_t o_list =
-      take(size_t(gnmr::kCounterSets) * size_t(gnmr::cand_list_cap(U)) * sizeof(int32_t));
+  // K2 has at most U workgroups, and at most 255 places for units past the last
+  const size_t o_prank = take((size_t(U) + 255) * sizeof(uint32_t));
+  const size_t o_punit = take((size_t(U) + 255) * sizeof(int32_t));
+  const size_t o_low = take(size_t(U) * sizeof(uint32_t));
+  const size_t o_cnt = take(size_t(U) * sizeof(uint64_t));
   const size_t o_gsum = take(size_t(U) * sizeof(double));
   const size_t o_st = take(sizeof(gnmr_stats));
   const size_t o_step = take(sizeof(int64_t));
@@ -496,11 +484,11 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   c->d_gnmr = reinterpret_cast<double*>(base + o_g);
   c->d_dgnmr = reinterpret_cast<double*>(base + o_d);
   c->d_risk = reinterpret_cast<double*>(base + o_r);
-  c->d_flags = reinterpret_cast<uint8_t*>(base + o_fl);
   c->d_mask = reinterpret_cast<uint8_t*>(base + o_mask);
-  c->d_keys = reinterpret_cast<uint64_t*>(base + o_keys);
-  c->d_counters = reinterpret_cast<int32_t*>(base + o_cnt);
-  c->d_cand_list = reinterpret_cast<int32_t*>(base + o_list);
+  c->d_pool_rank = reinterpret_cast<uint32_t*>(base + o_prank);
+  c->d_pool_unit = reinterpret_cast<int32_t*>(base + o_punit);
+  c->d_key_low = reinterpret_cast<uint32_t*>(base + o_low);
+  c->d_wg_counts = reinterpret_cast<uint64_t*>(base + o_cnt);
   c->d_gsum = reinterpret_cast<double*>(base + o_gsum);
   c->d_stats = reinterpret_cast<gnmr_stats*>(base + o_st);
   c->d_step = reinterpret_cast<int64_t*>(base + o_step);
@@ -540,9 +528,6 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   if (e == hipSuccess) e = hipMemsetAsync(c->d_gsum, 0, size_t(U) * sizeof(double), st);
   if (e == hipSuccess) e = hipMemsetAsync(c->d_stats, 0, sizeof(gnmr_stats), st);
   if (e == hipSuccess) e = hipMemsetAsync(c->d_step, 0, sizeof(int64_t), st);
-  if (e == hipSuccess)
-    e = hipMemsetAsync(c->d_counters, 0,
-                       size_t(gnmr::kCounterSets) * gnmr::kNumCounters * sizeof(int32_t), st);
   if (e == hipSuccess && S > 0)
     e = hipMemsetAsync(c->d_seg_base, 0, size_t(S) * sizeof(void*), st);
   // wait for what was enqueued also on failure: the uploads read host vectors
@@ -1062,7 +1047,7 @@ gnmr_status gnmr_actuator_create(gnmr_actuator** out, const gnmr_act_segment* se
     for (int64_t k = 0; k < num_segments; ++k)
       if (segs[k].cols <= gnmr::kK4NarrowCols) narrow_rows += segs[k].rows;
     if (narrow_rows > 4 * gnmr::kK4MaxWorkgroups || rows - narrow_rows > gnmr::kK4MaxWorkgroups)
-      return fail(GNMR_E_INVALID, "too many rows for one call: at most " +
+      return fail(GNMR_E_INVALID, "too many rows for one launch: at most " +
                                       std::to_string(4 * gnmr::kK4MaxWorkgroups) +
                                       " rows of up to 4096 features and " +
                                       std::to_string(gnmr::kK4MaxWorkgroups) + " longer rows");
@@ -1157,7 +1142,7 @@ gnmr_status gnmr_actuate_matrix(const void* in, void* out, int64_t rows, int32_t
   if (cols < 8 || cols > gnmr::kK4MaxCols || cols % 8 != 0)
     return fail(GNMR_E_INVALID, "cols must be a multiple of 8 in [8, 16384]");
   if (rows > (cols <= gnmr::kK4NarrowCols ? 4 : 1) * gnmr::kK4MaxWorkgroups)
-    return fail(GNMR_E_INVALID, "too many rows for one call: at most " +
+    return fail(GNMR_E_INVALID, "too many rows for one launch: at most " +
                                     std::to_string(4 * gnmr::kK4MaxWorkgroups) +
                                     " rows of up to 4096 features or " +
                                     std::to_string(gnmr::kK4MaxWorkgroups) + " longer rows");

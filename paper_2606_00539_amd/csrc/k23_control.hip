@@ -8,8 +8,10 @@
 //                  index), lock update and step counters (Alg. 2; Sec. 3.3,
 //                  3.4)
 //
-// Deterministic: fixed reduction orders, integer atomics only.
+// Deterministic: fixed reduction orders, integer atomics (in LDS) only.
 #include <math.h>
+
+#include <type_traits>
 
 #include "gnmr_internal.h"
 
@@ -22,6 +24,61 @@ __device__ __forceinline__ double wave_sum(double v) {
   for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
   return v;
 }
+
+// Scans and reductions of 32-bit values over a wavefront by data-parallel
+// primitives: four shifts inside the rows of 16 lanes, then the rows' last
+// lanes passed on (about 50 cycles, where six dependent lane permutes through
+// LDS take several hundred).
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
+  auto step = [&](auto ctrl, auto rows) {
+    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xF, false)));
+  };
+  constexpr int kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+  using std::integral_constant;
+  step(integral_constant<int, kShr + 1>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 2>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 4>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 8>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kBcast15>{}, integral_constant<int, 0xA>{});
+  step(integral_constant<int, kBcast31>{}, integral_constant<int, 0xC>{});
+  return x;
+}
+
+// Inclusive prefix sum over the lanes; the last lane holds the total.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  return wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+// The same inside each row of 16 lanes.
+template <typename Op>
+__device__ __forceinline__ uint32_t row_scan(uint32_t x, uint32_t identity, Op op) {
+  auto step = [&](auto ctrl) {
+    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
+                                                   0xF, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{});
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  return x;
+}
+
+__device__ __forceinline__ uint32_t row_prefix(uint32_t x) {
+  return row_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+__device__ __forceinline__ uint32_t lane_of(uint32_t x, int lane) {
+  return uint32_t(__builtin_amdgcn_readlane(int(x), lane));
+}
+
+struct Min {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
+};
+struct Max {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
+};
 
 // Fixed-order float64 sum of unit b's item partials by L lanes (lane < L):
 // each lane keeps four running sums over a stride-L walk, then the lanes are
@@ -84,14 +141,26 @@ __device__ __forceinline__ uint64_t cand_key(double R) {
   return uint64_t(__double_as_longlong(R)) + 1;
 }
 
-// What one unit adds to the step's counters and candidate list.
-struct Contrib {
-  bool cand, ranked, tg, td, tr, nonfinite;
+// A candidate's place in the ranking to 32 bits: the key's upper half and one
+// more, 0 for a unit that is active without ranking (key 0).  Units that are
+// equal here are told apart by the key's lower half.
+__device__ __forceinline__ uint32_t rank_of(uint64_t key) {
+  return key != 0 ? uint32_t(key >> 32) + 1u : 0u;
+}
+
+// One unit's step: what is stored for it, and its part in the counters and the
+// candidate pool.
+struct UnitStep {
+  double n, A, G, D, R, gsum;
+  uint64_t key;   // candidates: the ranking key, 0 when active without ranking
+  int32_t lock;   // Lock after the step if the unit is selected
+  int32_t slot;   // ring slot of the new GNMR
+  bool cand, tg, td, tr, finite;
 };
 
 // Alg. 1 and the risk of Alg. 2 for unit b given its norm n, and the unit's
-// membership of the candidate pool C_t; returns what it adds to the counters.
-__device__ __forceinline__ Contrib update_unit(const UpdateArgs& a, int b, double n) {
+// membership of the candidate pool C_t.  Stores nothing.
+__device__ __forceinline__ UnitStep update_unit(const UpdateArgs& a, int b, double n) {
   const int U = a.num_units;
   // The step counter lives on the device, so that a captured step replays
   // correctly: t = 1 + steps completed, the queue holds min(t - 1, delta)
@@ -117,126 +186,100 @@ __device__ __forceinline__ Contrib update_unit(const UpdateArgs& a, int b, doubl
     const double den = total / double(a.window) + a.eps;
     if (finite && den != 0.0) D = G / den;
   }
-  // Alg. 1: running mean and queue push (the new value replaces the oldest).
-  if (finite) a.A[b] = A_prev + (n - A_prev) / double(t);
-  a.Q[int64_t(slot0) * U + b] = finite ? G : 1.0;
+  // Alg. 1: running mean (and, in store_unit, the queue push: the new value
+  // replaces the oldest).
+  UnitStep u{};
+  u.n = n;
+  u.A = finite ? A_prev + (n - A_prev) / double(t) : A_prev;
+  u.slot = slot0;
+  u.finite = finite;
   if (!finite) G = D = INFINITY;
+  u.G = G;
+  u.D = D;
 
   // Alg. 2: R = max(GNMR / alpha, Delta-GNMR / beta); the pool C_t holds the
   // recoverable units with R > 1 or a lock left from the previous step.
   const double gt = G / a.alpha;
   const double dt = D / a.beta;
   const double R = gt > dt ? gt : dt;
+  u.R = R;
   const bool rec = a.rec[b] != 0;
   const bool trig = R > 1.0;
-  bool cand = rec && (trig || a.lock[b] > 0);
+  const int32_t prev_lock = a.lock[b];
+  const bool prev_active = a.mask[b] != 0;
+  bool cand = rec && (trig || prev_lock > 0);
   bool keep = false;
   double rank_by = R;
   if (a.static_set) {                 // static baseline: profile, rank once, hold
+    u.gsum = a.gsum[b];
     if (t <= a.warmup) {
-      a.gsum[b] += finite ? G : 0.0;
+      u.gsum += finite ? G : 0.0;
       cand = keep = rec;
     } else if (t == a.warmup + 1) {
       cand = rec;
-      rank_by = a.gsum[b] / double(a.warmup);   // mean GNMR over steps 1..W
+      rank_by = u.gsum / double(a.warmup);   // mean GNMR over steps 1..W
     } else {
-      cand = keep = a.mask[b] != 0;
+      cand = keep = prev_active;
     }
   } else if (warm) {                  // warm-up: C_t = A_t = B_rec
     cand = rec;
     keep = rec;
   } else if (a.admitted && cand) {    // admitted-only budget: A_{t-1} members stay
-    keep = a.mask[b] != 0;
+    keep = prev_active;
   }
-  const bool ranked = cand && !keep;
-  const bool tg = rec && gt > 1.0, td = rec && dt > 1.0, tr = rec && trig;
-  a.norm[b] = n;
-  a.gnmr[b] = G;
-  a.dgnmr[b] = D;
-  a.risk[b] = R;
-  a.keys[b] = ranked ? cand_key(rank_by) : 0;
-  a.flags[b] = uint8_t((gt > 1.0 ? kFlagTrigG : 0) | (dt > 1.0 ? kFlagTrigD : 0) |
-                       (finite ? 0 : kFlagNonFinite) | (trig ? kFlagTrigR : 0) |
-                       (rec ? kFlagRec : 0) | (cand ? kFlagCand : 0) |
-                       (keep ? kFlagKeep : 0));
-  // Alg. 2 outcome of a unit outside C_t is fixed already: low-cost path,
-  // Lock = 0.  K3 only has to rank and update the members of C_t.
-  if (!cand) {
-    a.mask[b] = 0;
-    if (a.lock[b] != 0) a.lock[b] = 0;
-  }
-  return Contrib{cand, ranked, tg, td, tr, !finite};
+  u.key = cand && !keep ? cand_key(rank_by) : 0;
+  u.lock = trig ? a.lock_len : (prev_lock > 0 ? prev_lock - 1 : 0);
+  u.cand = cand;
+  u.tg = rec && gt > 1.0;
+  u.td = rec && dt > 1.0;
+  u.tr = rec && trig;
+  return u;
 }
 
-// Adds the contributions of a workgroup's units (`has`: this thread holds
-// unit b) to counter set blockIdx.x % kCounterSets and appends its members
-// of C_t to that set's list: summed by ballot and LDS first, then one global
-// atomic per counter and workgroup (integer atomics: exact; the list order
-// is irrelevant to the selection).  Called by every thread of the workgroup.
-__device__ void publish(const UpdateArgs& a, bool has, int b, const Contrib& c) {
-  __shared__ int32_t s_cnt[kNumCounters];
-  __shared__ int32_t s_base;
-  const int tid = int(threadIdx.x), wl = tid & 63;
-  if (tid < kNumCounters) s_cnt[tid] = 0;
-  __syncthreads();
-  const uint64_t m_c = __ballot(has && c.cand);
-  const uint64_t m_k = __ballot(has && c.ranked), m_g = __ballot(has && c.tg);
-  const uint64_t m_d = __ballot(has && c.td), m_r = __ballot(has && c.tr);
-  const uint64_t m_n = __ballot(has && c.nonfinite);
-  int wave_base = 0;
-  if (wl == 0) {
-    if (m_c) wave_base = atomicAdd(&s_cnt[kCntCand], __popcll(m_c));
-    if (m_k) atomicAdd(&s_cnt[kCntRank], __popcll(m_k));
-    if (m_g) atomicAdd(&s_cnt[kCntTrigG], __popcll(m_g));
-    if (m_d) atomicAdd(&s_cnt[kCntTrigD], __popcll(m_d));
-    if (m_r) atomicAdd(&s_cnt[kCntTrigR], __popcll(m_r));
-    if (m_n) atomicAdd(&s_cnt[kCntNonFinite], __popcll(m_n));
-  }
-  wave_base = __shfl(wave_base, 0, 64);
-  const int slot = wave_base + __popcll(m_c & ((uint64_t(1) << wl) - 1));
-  __syncthreads();
-  const int set = int(blockIdx.x % kCounterSets);
-  if (tid == 0) {
-    int32_t* cs = a.counters + set * kNumCounters;
-    s_base = s_cnt[kCntCand] ? atomicAdd(&cs[kCntCand], s_cnt[kCntCand]) : 0;
-#pragma unroll
-    for (int k = 1; k < kNumCounters; ++k)
-      if (s_cnt[k]) atomicAdd(&cs[k], s_cnt[k]);
-  }
-  __syncthreads();
-  if (has && c.cand) a.cand_list[set * a.list_cap + s_base + slot] = b;
+// Everything of the step but the selection's outcome.
+__device__ __forceinline__ void store_unit(const UpdateArgs& a, int b, const UnitStep& u) {
+  a.A[b] = u.A;
+  a.Q[int64_t(u.slot) * a.num_units + b] = u.finite ? u.G : 1.0;
+  if (a.static_set) a.gsum[b] = u.gsum;
+  a.norm[b] = u.n;
+  a.gnmr[b] = u.G;
+  a.dgnmr[b] = u.D;
+  a.risk[b] = u.R;
 }
 
-// The same for a kernel of one workgroup whose counters and list are in LDS:
-// one LDS atomic per counter and wavefront, no barrier (the caller's next
-// barrier makes the results visible).
-__device__ __forceinline__ void publish_local(int32_t* cnt, int32_t* list, bool has, int b,
-                                              const Contrib& c) {
-  const int wl = int(threadIdx.x & 63);
-  const uint64_t m_c = __ballot(has && c.cand);
-  const uint64_t m_k = __ballot(has && c.ranked), m_g = __ballot(has && c.tg);
-  const uint64_t m_d = __ballot(has && c.td), m_r = __ballot(has && c.tr);
-  const uint64_t m_n = __ballot(has && c.nonfinite);
-  int base = 0;
-  if (wl == 0) {
-    if (m_c) base = atomicAdd(&cnt[kCntCand], __popcll(m_c));
-    if (m_k) atomicAdd(&cnt[kCntRank], __popcll(m_k));
-    if (m_g) atomicAdd(&cnt[kCntTrigG], __popcll(m_g));
-    if (m_d) atomicAdd(&cnt[kCntTrigD], __popcll(m_d));
-    if (m_r) atomicAdd(&cnt[kCntTrigR], __popcll(m_r));
-    if (m_n) atomicAdd(&cnt[kCntNonFinite], __popcll(m_n));
-  }
-  base = __shfl(base, 0, 64);
-  if (has && c.cand) list[base + __popcll(m_c & ((uint64_t(1) << wl) - 1))] = b;
+// The counters' contributions of one wavefront, kCountBits bits each: at most
+// 256 units per workgroup, so the sum over a workgroup's waves fits too.
+constexpr int kCountBits = 10;
+enum : int { kCntCand, kCntRank, kCntTrigG, kCntTrigD, kCntTrigR, kCntNonFinite };
+
+__device__ __forceinline__ int32_t count_of(uint64_t packed, int which) {
+  return int32_t(packed >> (which * kCountBits)) & ((1 << kCountBits) - 1);
+}
+
+__device__ __forceinline__ uint64_t wave_counts(bool has, const UnitStep& u) {
+  auto count = [&](bool x, int which) {
+    return uint64_t(__popcll(__ballot(has && x))) << (which * kCountBits);
+  };
+  return count(u.cand, kCntCand) | count(u.cand && u.key != 0, kCntRank) |
+         count(u.tg, kCntTrigG) | count(u.td, kCntTrigD) | count(u.tr, kCntTrigR) |
+         count(!u.finite, kCntNonFinite);
 }
 
 // K2: L lanes per unit sum its partials; lane 0 then runs Alg. 1, the risk of
-// Alg. 2, and marks the unit's membership of the candidate pool C_t.
+// Alg. 2, and marks the unit's membership of the candidate pool C_t.  Each
+// workgroup leaves its counts in one word and its members of C_t at the start
+// of its own part of the pool: no atomics (42,496 units: 4.2 us, 5.7 with one per
+// counter and workgroup on 64 sets of counters).  The mask and Lock are written as
+// if all of C_t were selected: K3 clears them for the members of C_t that the
+// budget leaves out.
 template <int L>
 __global__ __launch_bounds__(256) void k2_update(UpdateArgs a) {
+  constexpr int kUnits = 256 / L;  // per workgroup
   __shared__ double red[4];
-  const int lane = L == 1 ? 0 : int(threadIdx.x % L);
-  const int b = blockIdx.x * (256 / L) + threadIdx.x / L;
+  __shared__ uint64_t s_counts[4];
+  const int tid = int(threadIdx.x), wave = tid >> 6;
+  const int lane = L == 1 ? 0 : tid % L;
+  const int b = blockIdx.x * kUnits + tid / L;
   if (L == 256 && b >= a.num_units) return;  // the whole workgroup
   const bool in = b < a.num_units;           // uniform per wavefront when L = 64
   double n = 0.0;
@@ -248,398 +291,458 @@ __global__ __launch_bounds__(256) void k2_update(UpdateArgs a) {
     }
   }
   const bool has = in && lane == 0;
-  Contrib c{};
-  if (has) c = update_unit(a, b, n);
-  publish(a, has, b, c);
+  UnitStep u{};
+  if (has) u = update_unit(a, b, n);
+  const uint64_t members = __ballot(has && u.cand);
+  uint64_t mine = wave_counts(has, u);
+  int at = __popcll(members & ((uint64_t(1) << (tid & 63)) - 1));
+  if constexpr (L < 256) {  // (L = 256: the one unit is the first wave's)
+    if ((tid & 63) == 0) s_counts[wave] = mine;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) at += count_of(s_counts[w], kCntCand);
+    mine = ((s_counts[0] + s_counts[1]) + s_counts[2]) + s_counts[3];
+  }
+  if (tid == 0) a.wg_counts[blockIdx.x] = mine;
+  if (has) {
+    if (u.cand) {
+      a.pool_rank[blockIdx.x * kUnits + at] = rank_of(u.key);
+      a.pool_unit[blockIdx.x * kUnits + at] = b;
+      a.key_low[b] = uint32_t(u.key);
+    }
+    a.mask[b] = u.cand ? 1 : 0;
+    a.lock[b] = u.cand ? u.lock : 0;
+    store_unit(a, b, u);
+  }
 }
 
 constexpr int kK3Block = 1024;
-constexpr int kK3Cap = 12288;  // candidates held in LDS (144 KiB); larger pools use the global keys
+constexpr int kK3Cap = 16384;  // candidates held in LDS (128 KiB); larger pools are read again
 constexpr int kK3Count = 128;  // pools up to this size are ranked by direct counting
+constexpr int kK3Waves = kK3Block / 64;
 
-// Lock update of Alg. 2 for one unit given its selection.
-__device__ __forceinline__ void apply_selection(const SelectArgs& a, int b, bool sel, uint8_t f) {
-  int32_t L = 0;
-  if (sel) {
-    const int32_t prev = a.lock[b];
-    L = (f & kFlagTrigR) ? a.lock_len : (prev > 0 ? prev - 1 : 0);
-  }
-  a.lock[b] = L;
-  a.mask[b] = sel ? 1 : 0;
-}
+// The k-th largest value (Top_maxO's threshold) by a radix select: 11 bits per
+// pass, starting at the highest bit in which value - smallest differs, which
+// the few binades of R above 1 leave high in the word.  Once the bucket that
+// holds the k-th value has at most 64 members, those are gathered and the
+// workgroup finishes by counting, for each, the values above it: after one pass
+// for typical pools.
+constexpr int kDigit = 11;
+constexpr int kBins = 1 << kDigit;
+static_assert(kBins == 2 * kK3Block, "two bins per thread");
 
-// MSB-first radix select, 8 passes of 8 bits: the k-th largest (1-based) of
-// the n keys key_at(i), i < n.  Returns it as T; *rest receives how many keys
-// equal to T are among the k largest.  Called by every thread of the
-// workgroup.  Two barriers per pass: the histograms alternate between the
-// two halves of hist[512], so a pass clears the next pass's half (last read
-// before the previous pass's second barrier) while it counts into its own,
-// and the digit it publishes is read by every thread before any thread can
-// reach the barrier after which the next digit is written.
-//
-// Once the bucket that holds the k-th largest key has at most 64 keys, the
-// passes stop: those keys are gathered into LDS and one wavefront finishes by
-// counting, for each, the keys above it (a typical pool of a few thousand R
-// values gets there after 3 of the 8 passes).
-struct RadixSmall {
-  uint64_t key[64];
-  int n;                  // keys gathered
-  int bucket;             // keys in the chosen bucket (written with the digit)
-  uint64_t T;
-  int rest;
+struct SelectShared {
+  uint32_t hist[kBins];          // zero between passes
+  uint32_t lo[kK3Waves], hi[kK3Waves];
+  uint32_t above[kK3Waves];
+  uint64_t key[kK3Count];        // the small bucket's values, or the small pool's keys
+  int32_t unit[kK3Count];        // and units
+  uint32_t T, bin, k, bucket, n, rest, equal;
 };
 
-template <typename KeyAt>
-__device__ uint64_t radix_select(KeyAt key_at, int n, int k, uint32_t* hist, int* s_digit,
-                                 int* s_k, int* rest, RadixSmall* sm) {
-  const int tid = threadIdx.x;
-  uint64_t prefix = 0, pmask = 0;
-  if (tid < 256) hist[tid] = 0;
+struct Threshold {
+  uint32_t T;      // the k-th largest value
+  uint32_t rest;   // how many values equal to T are among the k largest
+  uint32_t equal;  // values equal to T
+};
+
+// Pool::each(f) calls f(rank, unit, valid) for each of this thread's candidates,
+// with the whole wavefront; val(rank, unit, v) says whether a candidate takes
+// part and sets its value v; lo and hi are the smallest and largest of this
+// thread's values (~0 and 0 for none).  Called by every thread of the
+// workgroup, with k <= the candidates that take part; sh.n is 0 and sh.hist
+// zero on entry and on return.
+template <typename Pool, typename Val>
+__device__ Threshold kth_largest(const Pool& pool, Val val, uint32_t k, uint32_t lo, uint32_t hi,
+                                 SelectShared& sh) {
+  static_assert(kK3Waves == 16, "a row of lanes per wave sums");
+  const int tid = int(threadIdx.x), l = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lo = wave_scan(lo, ~0u, Min{});
+  hi = wave_scan(hi, 0u, Max{});
+  if (l == 63) {
+    sh.lo[wave] = lo;
+    sh.hi[wave] = hi;
+  }
   __syncthreads();
-  for (int shift = 56, pass = 0; shift >= 0; shift -= 8, ++pass) {
-    uint32_t* const h = hist + (pass & 1) * 256;
-    if (tid < 256) hist[((pass + 1) & 1) * 256 + tid] = 0;
-    if (tid == 0) sm->n = 0;
-    // In the upper bytes of R's bits the keys of a wavefront mostly share
-    // one digit: then one lane adds them all (one LDS atomic, not one per key
-    // on the same counter); otherwise every key adds itself.
-    const int rounds = (n + kK3Block - 1) / kK3Block;
-    for (int r = 0; r < rounds; ++r) {
-      const int i = tid + r * kK3Block;
-      bool pend = false;
-      uint32_t d = 0;
-      if (i < n) {
-        const uint64_t key = key_at(i);
-        pend = (key & pmask) == prefix;
-        d = uint32_t(key >> shift) & 255u;
-      }
-      const uint64_t m = __ballot(pend);
-      if (m == 0) continue;
-      const int leader = __ffsll((unsigned long long)m) - 1;
-      const uint32_t dl = __shfl(d, leader, 64);
-      if (__ballot(pend && d == dl) == m) {
-        if ((tid & 63) == leader) atomicAdd(&h[dl], uint32_t(__popcll(m)));
-      } else if (pend) {
-        atomicAdd(&h[d], 1u);
-      }
+  lo = lane_of(row_scan(sh.lo[l & 15], ~0u, Min{}), 15);
+  hi = lane_of(row_scan(sh.hi[l & 15], 0u, Max{}), 15);
+  const int bits = hi > lo ? 32 - __clz(int(hi - lo)) : 1;
+  int shift = bits > kDigit ? bits - kDigit : 0, width = kDigit;
+  uint32_t prefix = 0;  // (value - lo) >> (shift + width) of the bucket
+  for (;;) {
+    const uint32_t digits = (1u << width) - 1u;
+    pool.each([&](uint32_t rank, int32_t unit, bool valid) {
+      uint32_t v = 0;
+      const bool in = valid && val(rank, unit, v);
+      const uint32_t d = (v - lo) >> shift;
+      if (in && (d >> width) == prefix) atomicAdd(&sh.hist[d & digits], 1u);
+    });
+    __syncthreads();
+    // The bin of the k-th largest: thread t holds bins 2t and 2t+1; sums over
+    // the threads give the members above them, and the one thread whose bins
+    // reach k names the bin.
+    const uint32_t h0 = sh.hist[2 * tid], h1 = sh.hist[2 * tid + 1], own = h0 + h1;
+    sh.hist[2 * tid] = sh.hist[2 * tid + 1] = 0;
+    const uint32_t sum = wave_prefix(own);
+    if (l == 63) sh.above[wave] = sum;
+    __syncthreads();
+    const uint32_t waves = row_prefix(sh.above[l & 15]);  // sums of waves 0 .. l
+    const uint32_t above = lane_of(waves, 15) - lane_of(waves, wave) + lane_of(sum, 63) - sum;
+    if (above < k && above + own >= k) {
+      const bool upper = above + h1 >= k;
+      sh.bin = uint32_t(2 * tid) + (upper ? 1u : 0u);
+      sh.k = k - above - (upper ? 0u : h1);
+      sh.bucket = upper ? h1 : h0;
     }
     __syncthreads();
-    if (tid < 64) {
-      // The digit of the k-th largest key: the largest d whose count of keys
-      // with a digit above d is below k, found by one wavefront: lane l holds
-      // digits 4l .. 4l+3, a suffix sum over the lanes gives the count above
-      // each lane's digits, and the one lane whose digits reach k names d
-      // (k <= the keys in the histogram, so exactly one lane does).
-      const int l = tid;
-      const uint32_t h0 = h[4 * l], h1 = h[4 * l + 1], h2 = h[4 * l + 2], h3 = h[4 * l + 3];
-      const uint32_t own = h0 + h1 + h2 + h3;
-      uint32_t suffix = own;  // keys with a digit >= 4l
+    prefix = (prefix << width) | sh.bin;
+    k = sh.k;
+    const uint32_t bucket = sh.bucket;
+    if (shift == 0) return Threshold{lo + prefix, k, bucket};
+    if (bucket <= 64) break;
+    width = shift < kDigit ? shift : kDigit;
+    shift -= width;
+  }
+  pool.each([&](uint32_t rank, int32_t unit, bool valid) {
+    uint32_t v = 0;
+    if (valid && val(rank, unit, v) && ((v - lo) >> shift) == prefix)
+      sh.key[atomicAdd(&sh.n, 1u)] = v;
+  });
+  __syncthreads();
+  {
+    // 16 threads a member, four comparisons each
+    static_assert(kK3Block == 64 * 16, "");
+    const uint32_t m = sh.n, i = uint32_t(tid) >> 4;
+    const uint32_t mine = i < m ? uint32_t(sh.key[i]) : 0;
+    uint32_t both = 0;  // members above (low half), and at or above
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_down(suffix, off, 64);
-        if (l + off < 64) suffix += v;
-      }
-      uint32_t above = suffix - own;  // keys with a digit above 4l+3
-      const uint32_t uk = uint32_t(k);
-      if (above < uk && above + own >= uk) {
-        int d = 4 * l + 3;
-        const uint32_t hv[4] = {h0, h1, h2, h3};
-        for (int j = 3; j > 0 && above + hv[j] < uk; --j, --d) above += hv[j];
-        *s_digit = d;
-        *s_k = k - int(above);
-        sm->bucket = int(d == 4 * l + 3 ? h3 : d == 4 * l + 2 ? h2 : d == 4 * l + 1 ? h1 : h0);
-      }
+    for (uint32_t j = uint32_t(tid) & 15u; j < 64; j += 16) {
+      const uint32_t vj = uint32_t(sh.key[j]);  // (stale past m)
+      both += j < m ? (vj > mine ? 1u : 0u) + (vj >= mine ? 0x10000u : 0u) : 0u;
     }
-    __syncthreads();
-    prefix |= uint64_t(*s_digit) << shift;
-    pmask |= uint64_t(255) << shift;
-    k = *s_k;
-    if (shift > 0 && sm->bucket <= 64) {
-      // gather the bucket (prefix matched so far) and finish by counting
-      for (int i = tid; i < n; i += kK3Block) {
-        const uint64_t key = key_at(i);
-        if ((key & pmask) == prefix) sm->key[atomicAdd(&sm->n, 1)] = key;
-      }
-      __syncthreads();
-      if (tid < 64) {
-        const int m = sm->n;
-        const uint64_t mine = tid < m ? sm->key[tid] : 0;
-        int above = 0, not_below = 0;
-        for (int j = 0; j < m; ++j) {
-          const uint64_t kj = sm->key[j];
-          above += kj > mine ? 1 : 0;
-          not_below += kj >= mine ? 1 : 0;
-        }
-        // the k-th largest: fewer than k keys above it, at least k at or above
-        if (tid < m && above < k && not_below >= k) {
-          sm->T = mine;
-          sm->rest = k - above;
-        }
-      }
-      __syncthreads();
-      *rest = sm->rest;
-      return sm->T;
-    }
-  }
-  *rest = k;
-  return prefix;
-}
-
-// Selection over every unit from the global keys: kept units, key > T, or
-// key == T and among the first `need` such units in index order (contiguous
-// index ranges per thread and an exclusive scan of their tie counts).
-__device__ int select_by_scan(const SelectArgs& a, uint64_t T, int need, uint32_t* scan) {
-  const int tid = threadIdx.x;
-  const int U = a.num_units;
-  const int per = (U + kK3Block - 1) / kK3Block;
-  const int lo = tid * per < U ? tid * per : U;
-  const int hi = lo + per < U ? lo + per : U;
-  uint32_t ties = 0;
-  for (int b = lo; b < hi; ++b) ties += a.keys[b] == T;
-  scan[tid] = ties;
-  __syncthreads();
-  for (int d = 1; d < kK3Block; d <<= 1) {
-    const uint32_t v = tid >= d ? scan[tid - d] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
-  }
-  uint32_t rank = scan[tid] - ties;  // ties before this thread's range
-  int c_act = 0;
-  for (int b = lo; b < hi; ++b) {
-    const uint64_t key = a.keys[b];
-    const uint8_t f = a.flags[b];
-    bool sel = key > T;
-    if (key == T) {
-      sel = rank < uint32_t(need);
-      ++rank;
-    }
-    sel = sel || (f & kFlagKeep);
-    apply_selection(a, b, sel, f);
-    c_act += sel;
-  }
-  return c_act;
-}
-
-// Ascending bitonic sort of v[0..kK3Block) in LDS by the whole workgroup.
-__device__ void bitonic_sort(int32_t* v) {
-  const int tid = threadIdx.x;
-  for (int size = 2; size <= kK3Block; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      __syncthreads();
-      const int j = tid ^ stride;
-      if (j > tid) {
-        const bool up = (tid & size) == 0;
-        const int32_t x = v[tid], y = v[j];
-        if ((x > y) == up) {
-          v[tid] = y;
-          v[j] = x;
-        }
-      }
+#pragma unroll
+    for (int x = 8; x >= 1; x >>= 1) both += __shfl_xor(both, x, 16);
+    const uint32_t above = both & 0xFFFFu, not_below = both >> 16;
+    // the k-th largest: fewer than k above it, at least k at or above
+    if (i < m && above < k && not_below >= k) {
+      sh.T = mine;
+      sh.rest = k - above;
+      sh.equal = not_below - above;
     }
   }
   __syncthreads();
+  if (tid == 0) sh.n = 0;
+  __syncthreads();
+  return Threshold{sh.T, sh.rest, sh.equal};
 }
 
-// K3: a single workgroup, over the members of C_t listed by K2.  Kept units
-// (warm-up; continuing units under the admitted-only budget) are active
-// without ranking; the others are ranked for the budget.  When at most maxO
-// are ranked they are all active.  Otherwise small pools (up to kK3Count)
-// count each candidate's place in the order directly; larger ones need the
-// maxO-th largest ranked key T (radix select; kept units carry
-// key 0): every ranked candidate with key > T is active, and the first
-// `need` with key == T in index order.  Pools of up to kCap candidates are
-// ranked in LDS; larger ones over the global keys of all units.
-template <int kCap>
-__device__ void select_body(const SelectArgs& a) {
-  __shared__ uint64_t c_key[kCap];
-  __shared__ int32_t c_idx[kCap];
-  __shared__ int32_t tie_idx[kK3Block];
-  __shared__ uint32_t hist[2 * 256];
-  __shared__ RadixSmall rsm;
-  __shared__ int cnt[2];  // active, ties
-  __shared__ int s_digit, s_k;
-  uint32_t* scan = reinterpret_cast<uint32_t*>(tie_idx);  // the global path reuses it
-  const int tid = threadIdx.x;
-  const int U = a.num_units;
-  // Gather K2's counter sets: totals, and where each set's candidates start
-  // in the pool's order (one thread per counter, then one for the offsets).
-  __shared__ int32_t s_sets[kCounterSets * kNumCounters];
-  __shared__ int32_t s_tot[kNumCounters];
-  __shared__ int32_t s_setoff[kCounterSets + 1];
-  if (tid < 2) cnt[tid] = 0;
-  if (a.num_sets == 1) {  // the single-workgroup kernel: one set, nothing to combine
-    if (tid < kNumCounters) s_tot[tid] = a.counters[tid];
-    if (tid == kNumCounters) {
-      s_setoff[0] = 0;
-      s_setoff[1] = a.counters[kCntCand];
-    }
-  } else {  // (num_sets is the same for the whole workgroup)
-    if (tid < a.num_sets * kNumCounters) s_sets[tid] = a.counters[tid];
-    __syncthreads();
-    if (tid < kNumCounters) {
-      int32_t t = 0;
-      for (int j = 0; j < a.num_sets; ++j) t += s_sets[j * kNumCounters + tid];
-      s_tot[tid] = t;
-    } else if (tid == kNumCounters) {
-      int32_t t = 0;
-      s_setoff[0] = 0;
-      for (int j = 0; j < a.num_sets; ++j) {
-        t += s_sets[j * kNumCounters + kCntCand];
-        s_setoff[j + 1] = t;
-      }
-    }
+// Top_maxO over the pool: drop(unit) for every ranked member of C_t that is not
+// in A_t.  Kept units (rank 0: warm-up; continuing units under the admitted-only
+// budget; the held static set) are active without ranking; the others are
+// ranked for the budget.  When at most maxO are ranked they are all active.
+// Otherwise pools of up to kK3Count count each candidate's place in the order (R
+// descending, index ascending) directly; larger ones take the maxO-th largest
+// rank, then, among the units that share it when not all of them may be taken,
+// that of the keys' lower halves (key_low(unit)), and then the index of the last
+// unit taken.  pool.lo, pool.hi: the smallest and largest of this thread's
+// nonzero ranks.
+template <typename Pool, typename Low, typename Drop>
+__device__ void select_pool(const Pool& pool, int n_cand, int n_rank, int max_o, Low key_low,
+                            SelectShared& sh, Drop drop) {
+  if (n_rank <= max_o) return;
+  if (max_o == 0) {
+    pool.each([&](uint32_t rank, int32_t unit, bool valid) {
+      if (valid && rank != 0) drop(unit);
+    });
+    return;
   }
-  __syncthreads();
-  const int n_cand = s_tot[kCntCand];
-  const int n_rank = s_tot[kCntRank];
-  // the i-th candidate of the pool: set j with s_setoff[j] <= i < s_setoff[j+1]
-  auto cand_at = [&](int i) {
-    int lo = 0, hi = a.num_sets;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s_setoff[mid] <= i) lo = mid; else hi = mid;
-    }
-    return a.cand_list[lo * a.list_cap + (i - s_setoff[lo])];
-  };
-
-  int c_act = 0;
-  if (a.max_o == 0 || n_rank <= a.max_o) {
-    // no ranking: every listed unit is active, or only the kept ones if maxO = 0
-    const bool take = a.max_o > 0;
-    for (int i = tid; i < n_cand; i += kK3Block) {
-      const int b = cand_at(i);
-      const uint8_t f = a.flags[b];
-      const bool sel = take || (f & kFlagKeep);
-      apply_selection(a, b, sel, f);
-      c_act += sel;
-    }
-  } else if (n_cand <= kK3Count) {
-    // A small pool: each ranked candidate's place in the order (R
-    // descending, index ascending) is counted directly against the whole
-    // pool, one barrier instead of the radix passes.  Kept units carry key
-    // 0, below every ranked key, so they never push a ranked one down; a
-    // ranked candidate is active when fewer than maxO candidates come before
-    // it.
-    if (tid < n_cand) {
-      const int b = cand_at(tid);
-      c_idx[tid] = b;
-      c_key[tid] = a.keys[b];
-    }
+  if (n_cand <= kK3Count) {
+    pool.each([&](uint32_t rank, int32_t unit, bool valid) {
+      if (!valid) return;
+      const uint32_t i = atomicAdd(&sh.n, 1u);
+      sh.key[i] = uint64_t(rank) << 32 | key_low(unit);
+      sh.unit[i] = unit;
+    });
     __syncthreads();
-    if (tid < n_cand) {
-      const int b = c_idx[tid];
-      const uint64_t key = c_key[tid];
+    const int i = int(threadIdx.x);
+    if (i < n_cand) {
+      const uint64_t key = sh.key[i];
+      const int32_t unit = sh.unit[i];
+      // kept units have rank 0, below every ranked key: none before a ranked one
       int before = 0;
 #pragma unroll 8
       for (int j = 0; j < n_cand; ++j) {
-        const uint64_t kj = c_key[j];
-        before += (kj > key || (kj == key && c_idx[j] < b)) ? 1 : 0;
+        const uint64_t kj = sh.key[j];
+        before += (kj > key || (kj == key && sh.unit[j] < unit)) ? 1 : 0;
       }
-      const uint8_t f = a.flags[b];
-      const bool sel = (key != 0 && before < a.max_o) || (f & kFlagKeep);
-      apply_selection(a, b, sel, f);
-      c_act += sel;
+      if ((key >> 32) != 0 && before >= max_o) drop(unit);
     }
-  } else if (n_cand > kCap) {
-    int need = 0;
-    const uint64_t* __restrict__ keys = a.keys;
-    const uint64_t T = radix_select([=](int i) { return keys[i]; }, U, a.max_o, hist, &s_digit,
-                                    &s_k, &need, &rsm);
-    c_act = select_by_scan(a, T, need, scan);
-  } else {
-    for (int i = tid; i < n_cand; i += kK3Block) {
-      const int b = cand_at(i);
-      c_idx[i] = b;
-      c_key[i] = a.keys[b];
-    }
-    __syncthreads();
-    int need = 0;
-    const uint64_t T = radix_select([&](int i) { return c_key[i]; }, n_cand, a.max_o, hist,
-                                    &s_digit, &s_k, &need, &rsm);
-    // Ties at T: gather their indices; when more tie than may be taken, keep
-    // the `need` smallest indices, i.e. every tie with index <= cut.
-    for (int i = tid; i < n_cand; i += kK3Block) {
-      if (c_key[i] == T) {
-        const int slot = atomicAdd(&cnt[1], 1);
-        if (slot < kK3Block) tie_idx[slot] = c_idx[i];
-      }
-    }
-    __syncthreads();
-    const int n_ties = cnt[1];
-    if (n_ties > kK3Block) {
-      c_act = select_by_scan(a, T, need, scan);
-    } else {
-      int32_t cut = INT32_MAX;  // every tie taken
-      if (n_ties > need) {
-        if (tid >= n_ties) tie_idx[tid] = INT32_MAX;
-        bitonic_sort(tie_idx);
-        cut = tie_idx[need - 1];
-      }
-      for (int i = tid; i < n_cand; i += kK3Block) {
-        const int b = c_idx[i];
-        const uint64_t key = c_key[i];
-        const uint8_t f = a.flags[b];
-        const bool sel = key > T || (key == T && b <= cut) || (f & kFlagKeep);
-        apply_selection(a, b, sel, f);
-        c_act += sel;
-      }
-    }
+    return;
   }
-  if (c_act) atomicAdd(&cnt[0], c_act);
-  __syncthreads();
-  if (tid == 0) {
-    const int64_t t = *a.step + 1;
-    const bool warm = t <= a.warmup;
-    gnmr_stats st;
-    st.t = t;
-    st.n_trig_gnmr = s_tot[kCntTrigG];
-    st.n_trig_dgnmr = s_tot[kCntTrigD];
-    st.n_trig = s_tot[kCntTrigR];
-    st.n_cand = n_cand;
-    st.n_active = cnt[0];
-    st.hit_maxo = (!warm && n_rank > 0 && n_rank >= a.max_o) ? 1 : 0;
-    st.n_nonfinite = s_tot[kCntNonFinite];
-    st.reserved = 0;
-    *a.stats = st;
-    *a.step = t;
+  const Threshold by_rank = kth_largest(
+      pool,
+      [](uint32_t rank, int32_t, uint32_t& v) {
+        v = rank;
+        return rank != 0;
+      },
+      uint32_t(max_o), pool.lo, pool.hi, sh);
+  const uint32_t T = by_rank.T;
+  uint32_t low_cut = 0;          // among rank T: every lower half,
+  int32_t unit_cut = INT32_MAX;  // and among rank T and that lower half: every unit
+  if (by_rank.rest < by_rank.equal) {
+    const Threshold by_low = kth_largest(
+        pool,
+        [&](uint32_t rank, int32_t unit, uint32_t& v) {
+          if (rank != T) return false;
+          v = key_low(unit);
+          return true;
+        },
+        by_rank.rest, 0u, ~0u, sh);
+    low_cut = by_low.T;
+    if (by_low.rest < by_low.equal)
+      unit_cut = int32_t(~kth_largest(
+                              pool,
+                              [&](uint32_t rank, int32_t unit, uint32_t& v) {
+                                v = ~uint32_t(unit);
+                                return rank == T && key_low(unit) == low_cut;
+                              },
+                              by_low.rest, 0u, ~0u, sh)
+                              .T);
   }
-  // the counter sets, ready for the next step (read only in the gather above)
-  for (int k = tid; k < a.num_sets * kNumCounters; k += kK3Block) a.counters[k] = 0;
+  const bool all_of_T = by_rank.rest == by_rank.equal;
+  pool.each([&](uint32_t rank, int32_t unit, bool valid) {
+    if (!valid || rank == 0 || rank > T || (rank == T && all_of_T)) return;
+    if (rank == T) {
+      const uint32_t low = key_low(unit);
+      if (low > low_cut || (low == low_cut && unit <= unit_cut)) return;
+    }
+    drop(unit);
+  });
 }
 
-__global__ __launch_bounds__(kK3Block) void k3_select(SelectArgs a) { select_body<kK3Cap>(a); }
+// One candidate per thread.
+struct OwnPool {
+  uint32_t rank;
+  int32_t unit;
+  bool valid;
+  uint32_t lo, hi;
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+    f(rank, unit, valid);
+  }
+};
+
+struct LdsPool {
+  const uint32_t* rank;
+  const int32_t* unit;
+  int n;
+  uint32_t lo, hi;
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+    for (int base = 0; base < n; base += kK3Block) {
+      const int i = base + int(threadIdx.x);
+      f(i < n ? rank[i] : 0, i < n ? unit[i] : 0, i < n);
+    }
+  }
+};
+
+// Larger pools: every place of every K2 workgroup, read again for every pass.
+struct GlobalPool {
+  const uint32_t* pool_rank;
+  const int32_t* pool_unit;
+  const uint64_t* wg_counts;
+  int places, shift;
+  uint32_t lo, hi;
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+    for (int base = 0; base < places; base += kK3Block) {
+      const int i = base + int(threadIdx.x);
+      const bool valid =
+          i < places && (i & ((1 << shift) - 1)) < count_of(wg_counts[i >> shift], kCntCand);
+      f(valid ? pool_rank[i] : 0, valid ? pool_unit[i] : 0, valid);
+    }
+  }
+};
+
+// Four bytes a lane straight to LDS: lane l's to p[l] (p the same for the wave).
+template <typename T>
+__device__ __forceinline__ void load_to_lds(const T* from, T* p) {
+  __builtin_amdgcn_global_load_lds((const void*)from,
+                                   (__attribute__((address_space(3))) void*)p, 4, 0, 0);
+}
+
+// Keeps the smallest and largest nonzero rank.
+__device__ __forceinline__ void widen_range(uint32_t rank, uint32_t& lo, uint32_t& hi) {
+  lo = rank != 0 && rank < lo ? rank : lo;
+  hi = rank > hi ? rank : hi;
+}
+
+// The counters of step t, by thread 0.
+__device__ __forceinline__ void finish_step(const SelectArgs& a, int64_t t,
+                                            const int32_t (&tot)[6]) {
+  const int32_t n_cand = tot[kCntCand], n_rank = tot[kCntRank];
+  const bool warm = t <= a.warmup;
+  gnmr_stats st;
+  st.t = t;
+  st.n_trig_gnmr = tot[kCntTrigG];
+  st.n_trig_dgnmr = tot[kCntTrigD];
+  st.n_trig = tot[kCntTrigR];
+  st.n_cand = n_cand;
+  // the kept units, and as many ranked ones as the budget takes
+  st.n_active = n_cand - n_rank + (n_rank < a.max_o ? n_rank : a.max_o);
+  st.hit_maxo = (!warm && n_rank > 0 && n_rank >= a.max_o) ? 1 : 0;
+  st.n_nonfinite = tot[kCntNonFinite];
+  st.reserved = 0;
+  *a.stats = st;
+  *a.step = t;
+}
+
+// K3: a single workgroup, over the members of C_t that K2's workgroups left.
+// When the budget takes them all it only adds up the counters.  Bound by
+// latency: one load for the counts, one batch of loads for the pool (ranks and
+// units; nothing is looked up per candidate unless ranks tie at the cut), then LDS
+// passes.  The instruction cache starts cold, so loops stay rolled and sums over
+// the waves are rows of lanes: unrolled 12 to a thread the same steps took 11 to
+// 12 us.  42,496 units with a pool of about 4,000 for maxO = 64: 8.8 us (19.4
+// with keys, flags and locks gathered per unit through 64 lists and 8-bit passes
+// over 64-bit keys); no ranking: 4.0 us.
+__global__ __launch_bounds__(kK3Block) void k3_select(SelectArgs a) {
+  __shared__ SelectShared sh;
+  __shared__ int32_t s_off[kK3Block + 1];  // first candidate of each thread's workgroups
+  __shared__ uint32_t s_wave[6 * kK3Waves];
+  __shared__ uint32_t s_rank[kK3Cap];
+  __shared__ int32_t s_unit[kK3Cap];
+  const int tid = int(threadIdx.x), l = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t t_now = *a.step + 1;
+  sh.hist[2 * tid] = sh.hist[2 * tid + 1] = 0;
+  if (tid == 0) sh.n = 0;
+  // Thread t counts for K2 workgroups [t * per, (t + 1) * per).
+  const int per = (a.num_wgs + kK3Block - 1) / kK3Block;
+  uint32_t sum[6] = {};
+  for (int w = tid * per; w < (tid + 1) * per && w < a.num_wgs; ++w) {
+    const uint64_t v = a.wg_counts[w];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sum[k] += uint32_t(count_of(v, k));
+  }
+  const uint32_t own = sum[kCntCand];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) sum[k] = wave_prefix(sum[k]);
+  if (l == 63)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s_wave[k * kK3Waves + wave] = sum[k];
+  __syncthreads();
+  // a row of 16 lanes per counter: its sums over the waves
+  const uint32_t first4 = row_prefix(s_wave[l]), last2 = row_prefix(s_wave[64 + (l & 31)]);
+  const int32_t tot[6] = {
+      int32_t(lane_of(first4, 15)), int32_t(lane_of(first4, 31)), int32_t(lane_of(first4, 47)),
+      int32_t(lane_of(first4, 63)), int32_t(lane_of(last2, 15)),  int32_t(lane_of(last2, 31))};
+  const int n_cand = tot[kCntCand];
+  if (tot[kCntRank] > a.max_o) {
+    auto drop = [&](int32_t unit) {
+      a.mask[unit] = 0;
+      a.lock[unit] = 0;
+    };
+    auto key_low = [&](int32_t unit) { return a.key_low[unit]; };
+    uint32_t lo = ~0u, hi = 0;
+    s_off[tid] = int32_t((wave > 0 ? lane_of(first4, wave - 1) : 0u) + sum[kCntCand] - own);
+    if (tid == 0) s_off[kK3Block] = n_cand;
+    __syncthreads();
+    if (n_cand <= kK3Cap) {
+      if (a.wg_shift >= 6 && per == 1) {
+        // K2 workgroups of 256 units: a wavefront each, straight to LDS, so that
+        // all of the loads are in flight and the loop stays small
+        for (int w = wave; w < a.num_wgs; w += kK3Waves) {
+          const int off = __builtin_amdgcn_readfirstlane(s_off[w]);
+          const int cnt = __builtin_amdgcn_readfirstlane(s_off[w + 1]) - off;
+          const int64_t first = int64_t(w) << a.wg_shift;
+          for (int j = 0; j < cnt; j += 64) {
+            if (j + l < cnt) {
+              load_to_lds(a.pool_rank + first + j + l, s_rank + off + j);
+              load_to_lds(a.pool_unit + first + j + l, s_unit + off + j);
+            }
+          }
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+      } else {
+        // smaller workgroups, or more of them than threads: one to 64 threads each
+        const int group = a.wg_shift < 6 ? 1 << a.wg_shift : 64;
+        for (int t = tid / group; t * per < a.num_wgs; t += kK3Block / group) {
+          int off = s_off[t];
+          for (int w = t * per; w < (t + 1) * per && w < a.num_wgs; ++w) {
+            const int cnt = count_of(a.wg_counts[w], kCntCand);
+            for (int j = tid & (group - 1); j < cnt; j += group) {
+              s_rank[off + j] = a.pool_rank[(int64_t(w) << a.wg_shift) + j];
+              s_unit[off + j] = a.pool_unit[(int64_t(w) << a.wg_shift) + j];
+            }
+            off += cnt;
+          }
+        }
+      }
+      __syncthreads();
+      LdsPool pool{s_rank, s_unit, n_cand, 0, 0};
+      pool.each([&](uint32_t rank, int32_t, bool) { widen_range(rank, lo, hi); });
+      pool.lo = lo;
+      pool.hi = hi;
+      select_pool(pool, n_cand, tot[kCntRank], a.max_o, key_low, sh, drop);
+    } else {
+      GlobalPool pool{a.pool_rank, a.pool_unit, a.wg_counts, a.num_wgs << a.wg_shift, a.wg_shift, 0, 0};
+      pool.each([&](uint32_t rank, int32_t, bool) { widen_range(rank, lo, hi); });
+      pool.lo = lo;
+      pool.hi = hi;
+      select_pool(pool, n_cand, tot[kCntRank], a.max_o, key_low, sh, drop);
+    }
+  }
+  if (tid == 0) finish_step(a, t_now, tot);
+}
 
 // K2 and K3 in one workgroup, for small workloads: at most kK3Block units,
 // each summed by one thread exactly as k2_update<1> sums it (or given its
-// norm), then the selection of K3 after a workgroup barrier, which makes
-// K2's keys and flags visible to every thread.  The counters and the
-// candidate list live in LDS here (one workgroup uses them), which keeps
-// global atomics off the path.  One launch instead of two; the same
-// arithmetic, so the same results.
+// norm), and the selection of K3 with every thread's candidate in its own
+// registers.  One launch instead of two; the same arithmetic, so the same
+// results.  Nothing is stored before the end, so that no barrier waits for a
+// store.
 __global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s) {
-  __shared__ int32_t s_counters[kNumCounters];
-  __shared__ int32_t s_cand[kK3Block];
-  if (threadIdx.x < kNumCounters) s_counters[threadIdx.x] = 0;
-  // one counter set, in LDS
-  u.counters = s.counters = s_counters;
-  u.cand_list = s_cand;
-  s.cand_list = s_cand;
-  u.list_cap = s.list_cap = kK3Block;
-  s.num_sets = 1;
-  __syncthreads();
+  __shared__ SelectShared sh;
+  __shared__ uint64_t s_counts[kK3Waves];
+  __shared__ uint8_t s_out[kK3Block];
   const int b = int(threadIdx.x);
+  const int64_t t_now = *s.step + 1;
+  sh.hist[2 * b] = sh.hist[2 * b + 1] = 0;
+  if (b == 0) sh.n = 0;
+  s_out[b] = 0;
   const bool has = b < u.num_units;
-  Contrib c{};
+  UnitStep x{};
   if (has) {
     const double n = u.ext_norm != nullptr
                          ? u.ext_norm[b]
                          : norm_of_sumsq(unit_ss<1>(u.unit_item_off, u.partial, b, 0, nullptr));
-    c = update_unit(u, b, n);
+    x = update_unit(u, b, n);
   }
-  publish_local(s_counters, s_cand, has, b, c);
+  const uint64_t mine = wave_counts(has, x);
+  if ((b & 63) == 0) s_counts[b >> 6] = mine;
   __syncthreads();
-  select_body<kK3Block>(s);  // at most kK3Block units, so the pool fits
+  int32_t tot[6] = {};
+#pragma unroll
+  for (int w = 0; w < kK3Waves; ++w)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) tot[k] += count_of(s_counts[w], k);
+  bool active = has && x.cand;
+  uint32_t lo = ~0u, hi = 0;
+  const uint32_t rank = rank_of(x.key);  // (0 for other than ranked candidates)
+  widen_range(rank, lo, hi);
+  // (a thread's own candidate is the only one whose key it is asked for; it
+  // is told through LDS that it is out, by whichever thread ranked it)
+  select_pool(OwnPool{rank, b, active, lo, hi}, tot[kCntCand], tot[kCntRank], s.max_o,
+              [&](int32_t) { return uint32_t(x.key); }, sh, [&](int32_t unit) { s_out[unit] = 1; });
+  __syncthreads();
+  active = active && s_out[b] == 0;
+  if (has) {
+    u.mask[b] = active ? 1 : 0;
+    u.lock[b] = active ? x.lock : 0;
+    store_unit(u, b, x);
+  }
+  if (b == 0) finish_step(s, t_now, tot);
 }
 
 }  // namespace
@@ -675,14 +778,24 @@ hipError_t launch_unit_sumsq(const int64_t* unit_item_off, const float* partial,
   return hipGetLastError();
 }
 
-hipError_t launch_update(const UpdateArgs& a, int64_t num_items, hipStream_t s) {
+hipError_t launch_update(const UpdateArgs& a, int64_t num_items, SelectArgs* sel, hipStream_t s) {
   const int L = a.ext_norm != nullptr ? 1 : lanes_per_unit(num_items, a.num_units);
+  const dim3 grid = L == 1    ? unit_grid<1>(a.num_units)
+                    : L == 64 ? unit_grid<64>(a.num_units)
+                              : unit_grid<256>(a.num_units);
+  sel->num_wgs = int32_t(grid.x);
+  sel->wg_shift = L == 1 ? 8 : L == 64 ? 2 : 0;
   if (L == 1)
-    hipLaunchKernelGGL(k2_update<1>, unit_grid<1>(a.num_units), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k2_update<1>, grid, dim3(256), 0, s, a);
   else if (L == 64)
-    hipLaunchKernelGGL(k2_update<64>, unit_grid<64>(a.num_units), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k2_update<64>, grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(k2_update<256>, unit_grid<256>(a.num_units), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k2_update<256>, grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k3_select, dim3(1), dim3(kK3Block), 0, s, a);
   return hipGetLastError();
 }
 
@@ -693,11 +806,6 @@ bool single_launch_update_select(const UpdateArgs& a, int64_t num_items) {
 
 hipError_t launch_update_select(const UpdateArgs& u, const SelectArgs& s, hipStream_t st) {
   hipLaunchKernelGGL(k23_small, dim3(1), dim3(kK3Block), 0, st, u, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k3_select, dim3(1), dim3(kK3Block), 0, s, a);
   return hipGetLastError();
 }
 
