@@ -123,8 +123,13 @@ hipError_t launch_actuate(const RowItem* items, const int64_t* class_off, int64_
 // One [rows][sg.cols] matrix, no row table.
 hipError_t launch_actuate_matrix(const ActSeg& sg, int64_t rows, const uint8_t* mask,
                                  int fmt_low, int fmt_rec, hipStream_t s);
-hipError_t launch_sumsq(const Item* items, int64_t num_items, const char* const* seg_base,
-                        const int32_t* seg_dtype, float* partial, hipStream_t s);
+// K1 over the items; the segments' addresses from the device table seg_base, or,
+// when ptrs is not null, from that host array of num_segs <= kK1MostPassed, which
+// goes with the launch and is also left in seg_base.
+constexpr int kK1FewPassed = 64, kK1MostPassed = 448;
+hipError_t launch_sumsq(const Item* items, int64_t num_items, const char** seg_base,
+                        const void* const* ptrs, int64_t num_segs, const int32_t* seg_dtype,
+                        float* partial, hipStream_t s);
 hipError_t launch_unit_sumsq(const int64_t* unit_item_off, const float* partial,
                              int64_t num_items, int32_t num_units, double* out, hipStream_t s);
 hipError_t launch_update(const UpdateArgs& a, int64_t num_items, SelectArgs* sel, hipStream_t s);

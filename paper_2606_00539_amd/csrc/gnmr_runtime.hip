@@ -260,8 +260,11 @@ gnmr_status check_ptrs(const gnmr_ctx* c, const void* const* ptrs) {
   return check_seg_ptrs(c->S, c->seg_numel.data(), c->seg_dtype.data(), ptrs);
 }
 
-// Copies this step's segment pointers to the device table on `st`.
-gnmr_status bind_ptrs(gnmr_ctx* c, const void* const* ptrs, hipStream_t st) {
+// Checks this step's segment pointers and copies them to the device table on
+// `st`; or, when they are few enough to go with the K1 launch and `passed` is
+// given, leaves them in *passed for it.
+gnmr_status bind_ptrs(gnmr_ctx* c, const void* const* ptrs, hipStream_t st,
+                      const void* const** passed = nullptr) {
   if (ptrs == nullptr) {
     if (!c->ptrs_bound && c->num_items > 0)
       return fail(GNMR_E_INVALID, "no segment pointers bound: pass seg_ptr");
@@ -270,6 +273,11 @@ gnmr_status bind_ptrs(gnmr_ctx* c, const void* const* ptrs, hipStream_t st) {
   gnmr_status r = check_ptrs(c, ptrs);
   if (r != GNMR_OK) return r;
   if (c->S == 0) return GNMR_OK;
+  if (passed != nullptr && c->num_items > 0 && c->S <= gnmr::kK1MostPassed) {
+    *passed = ptrs;
+    c->ptrs_bound = true;
+    return GNMR_OK;
+  }
   if (c->upload_pending) {
     GNMR_HIP(hipEventSynchronize(c->upload_done));
     c->upload_pending = false;
@@ -564,12 +572,13 @@ gnmr_status gnmr_step(gnmr_ctx* ctx, double alpha_t, double beta_t, const void* 
   DeviceGuard g(ctx->device);
   if (!g.ok) return fail(GNMR_E_HIP, "cannot select the context's device");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  r = bind_ptrs(ctx, seg_ptr, st);
+  const void* const* passed = nullptr;
+  r = bind_ptrs(ctx, seg_ptr, st, &passed);
   if (r != GNMR_OK) return r;
   r = record(ctx, 0, st);
   if (r != GNMR_OK) return r;
-  GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, ctx->d_seg_dtype,
-                              ctx->d_partial, st));
+  GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
+                              ctx->d_seg_dtype, ctx->d_partial, st));
   r = record(ctx, 1, st);
   if (r != GNMR_OK) return r;
   return update_and_select(ctx, nullptr, ctx->d_partial, ctx->d_unit_item_off, ctx->num_items,
@@ -728,10 +737,11 @@ gnmr_status gnmr_sumsq(gnmr_ctx* ctx, const void* const* seg_ptr, double* d_sums
   DeviceGuard g(ctx->device);
   if (!g.ok) return fail(GNMR_E_HIP, "cannot select the context's device");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  gnmr_status r = bind_ptrs(ctx, seg_ptr, st);
+  const void* const* passed = nullptr;
+  gnmr_status r = bind_ptrs(ctx, seg_ptr, st, &passed);
   if (r != GNMR_OK) return r;
-  GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, ctx->d_seg_dtype,
-                              ctx->d_partial, st));
+  GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
+                              ctx->d_seg_dtype, ctx->d_partial, st));
   GNMR_HIP(gnmr::launch_unit_sumsq(ctx->d_unit_item_off, ctx->d_partial, ctx->num_items,
                                    ctx->U, d_sumsq, st));
   return GNMR_OK;
@@ -822,7 +832,7 @@ gnmr_status gnmr_sumsq_noalloc(int32_t num_units, const gnmr_segments* segs, dou
   // read the old work list before it is replaced
   GNMR_HIP(hipMemcpyAsync(base, blob.data(), blob.size(), hipMemcpyHostToDevice, st));
   hipError_t e = gnmr::launch_sumsq(reinterpret_cast<const Item*>(base + o_items), n_items,
-                                    reinterpret_cast<const char* const*>(base + o_base),
+                                    reinterpret_cast<const char**>(base + o_base), nullptr, S,
                                     reinterpret_cast<const int32_t*>(base + o_dt),
                                     reinterpret_cast<float*>(base + o_part), st);
   if (e == hipSuccess)

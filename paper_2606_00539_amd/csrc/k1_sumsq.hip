@@ -4,6 +4,8 @@
 //
 // Deterministic: fixed work items, a fixed reduction tree, no floating-point
 // atomics; the result does not depend on the grid or on scheduling.
+#include <string.h>
+
 #include "gnmr_internal.h"
 
 namespace gnmr {
@@ -101,16 +103,37 @@ __device__ __forceinline__ uint32_t xcd_item(uint32_t w, uint32_t num_items) {
   return x * q + (x < r ? x : r) + j;
 }
 
+// The segments' addresses: from a table in device memory, or from the kernel's
+// own arguments, which the first workgroup then copies to that table for later
+// steps.
+struct TableBases {
+  const char* const* table;
+  __device__ __forceinline__ const char* of(int32_t seg) const { return table[seg]; }
+  __device__ __forceinline__ void keep() const {}
+};
+template <int kMost>
+struct PassedBases {
+  const char** table;
+  int32_t num;
+  const char* base[kMost];
+  __device__ __forceinline__ const char* of(int32_t seg) const { return base[seg]; }
+  __device__ __forceinline__ void keep() const {
+    if (blockIdx.x == 0)
+      for (int i = int(threadIdx.x); i < num; i += kK1Block) table[i] = base[i];
+  }
+};
+
+template <typename Bases>
 __global__ __launch_bounds__(kK1Block) void k1_sumsq(const Item* __restrict__ items,
-                                                     uint32_t num_items,
-                                                     const char* const* __restrict__ seg_base,
+                                                     uint32_t num_items, const Bases seg_base,
                                                      const int32_t* __restrict__ seg_dtype,
                                                      float* __restrict__ partial) {
   const uint32_t item = xcd_item(blockIdx.x, num_items);
   const Item it = items[item];
+  seg_base.keep();
   const int dt = seg_dtype[it.seg];
   const uintptr_t esz = dt == GNMR_BF16 ? 2 : 4;
-  const uintptr_t b0 = reinterpret_cast<uintptr_t>(seg_base[it.seg]) + uintptr_t(it.e0) * esz;
+  const uintptr_t b0 = reinterpret_cast<uintptr_t>(seg_base.of(it.seg)) + uintptr_t(it.e0) * esz;
   const uintptr_t b1 = b0 + uintptr_t(it.count) * esz;
   // [b0, a0) head and [a1, b1) tail are under 16 bytes each; [a0, a1) is the
   // 16-byte-aligned body.  An item inside one 16-byte window is all head.
@@ -151,11 +174,33 @@ __global__ __launch_bounds__(kK1Block) void k1_sumsq(const Item* __restrict__ it
 
 }  // namespace
 
-hipError_t launch_sumsq(const Item* items, int64_t num_items, const char* const* seg_base,
-                        const int32_t* seg_dtype, float* partial, hipStream_t s) {
+namespace {
+
+template <int kMost>
+void launch_passed(const Item* items, int64_t num_items, const char** table,
+                   const void* const* ptrs, int64_t num_segs, const int32_t* seg_dtype,
+                   float* partial, hipStream_t s) {
+  PassedBases<kMost> b;
+  b.table = table;
+  b.num = int32_t(num_segs);
+  memcpy(b.base, ptrs, size_t(num_segs) * sizeof(void*));
+  hipLaunchKernelGGL(k1_sumsq<PassedBases<kMost>>, dim3(unsigned(num_items)), dim3(kK1Block), 0, s,
+                     items, uint32_t(num_items), b, seg_dtype, partial);
+}
+
+}  // namespace
+
+hipError_t launch_sumsq(const Item* items, int64_t num_items, const char** seg_base,
+                        const void* const* ptrs, int64_t num_segs, const int32_t* seg_dtype,
+                        float* partial, hipStream_t s) {
   if (num_items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k1_sumsq, dim3(unsigned(num_items)), dim3(kK1Block), 0, s, items,
-                     uint32_t(num_items), seg_base, seg_dtype, partial);
+  if (ptrs == nullptr)
+    hipLaunchKernelGGL(k1_sumsq<TableBases>, dim3(unsigned(num_items)), dim3(kK1Block), 0, s, items,
+                       uint32_t(num_items), TableBases{seg_base}, seg_dtype, partial);
+  else if (num_segs <= kK1FewPassed)
+    launch_passed<kK1FewPassed>(items, num_items, seg_base, ptrs, num_segs, seg_dtype, partial, s);
+  else
+    launch_passed<kK1MostPassed>(items, num_items, seg_base, ptrs, num_segs, seg_dtype, partial, s);
   return hipGetLastError();
 }
 
