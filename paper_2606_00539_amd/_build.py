@@ -11,7 +11,7 @@ LIB = os.path.join(PKG, "libgnmr.so")
 SOURCES = [os.path.join(PKG, "csrc", f)
            for f in ("gnmr_runtime.hip", "k1_sumsq.hip", "k23_control.hip", "k4_actuator.hip",
                      "k5_wgrad.hip")]
-HEADERS = [os.path.join(PKG, "csrc", f) for f in ("gnmr_internal.h", "k1_geometry.h")] + [
+HEADERS = [os.path.join(PKG, "csrc", f) for f in ("gnmr_internal.h", "k1_geometry.h", "lane_ops.h")] + [
     os.path.join(ROOT, "include", "gnmr.h")]
 
 # Packed-fp32 instructions are switched off for all device code.

@@ -349,7 +349,7 @@ gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* 
   gnmr_status r = GNMR_OK;
   if (gnmr::single_launch_update_select(u, num_parts)) {
     // small workload: K2 + K3 in one launch (timed as the update; select 0)
-    GNMR_HIP(gnmr::launch_update_select(u, s, st));
+    GNMR_HIP(gnmr::launch_update_select(u, s, num_parts, st));
     r = record(c, 2, st);
     if (r == GNMR_OK) r = record(c, 3, st);
     if (r != GNMR_OK) return r;

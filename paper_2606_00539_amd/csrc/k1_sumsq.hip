@@ -7,19 +7,13 @@
 #include <string.h>
 
 #include "gnmr_internal.h"
+#include "lane_ops.h"
 
 namespace gnmr {
 namespace {
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// Butterfly over the 64 lanes of a wavefront; every lane ends with the same sum.
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
 
 // One 16-byte load as a native vector (loads through address-space-1
 // pointers need a plain vector type, not HIP's uint4 class).

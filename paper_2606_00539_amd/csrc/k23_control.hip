@@ -14,16 +14,10 @@
 #include <type_traits>
 
 #include "gnmr_internal.h"
+#include "lane_ops.h"
 
 namespace gnmr {
 namespace {
-
-// Butterfly over the 64 lanes of a wavefront; every lane ends with the same sum.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
 
 // Scans and reductions of 32-bit values over a wavefront by data-parallel
 // primitives: four shifts inside the rows of 16 lanes, then the rows' last
@@ -84,13 +78,9 @@ struct Max {
 // each lane keeps four running sums over a stride-L walk, then the lanes are
 // combined by a fixed butterfly (L = 64) and a fixed cross-wave order
 // (L = 256).  L = 1 is one thread per unit, for units of few items.
-template <int L>
-__device__ __forceinline__ double unit_ss(const int64_t* __restrict__ off,
-                                          const float* __restrict__ partial, int b, int lane,
-                                          double* red) {
+template <int L, typename Index>
+__device__ __forceinline__ double lane_ss(const float* partial, Index i, Index hi) {
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  const int64_t hi = off[b + 1];
-  int64_t i = off[b] + lane;
   for (; i + 3 * L < hi; i += 4 * L) {
     const float a = partial[i], c = partial[i + L], d = partial[i + 2 * L], e = partial[i + 3 * L];
     s0 += double(a);
@@ -99,7 +89,14 @@ __device__ __forceinline__ double unit_ss(const int64_t* __restrict__ off,
     s3 += double(e);
   }
   for (; i < hi; i += L) s0 += double(partial[i]);
-  const double s = (s0 + s1) + (s2 + s3);
+  return (s0 + s1) + (s2 + s3);
+}
+
+template <int L>
+__device__ __forceinline__ double unit_ss(const int64_t* __restrict__ off,
+                                          const float* __restrict__ partial, int b, int lane,
+                                          double* red) {
+  const double s = lane_ss<L, int64_t>(partial, off[b] + lane, off[b + 1]);
   if constexpr (L == 1) {
     return s;
   } else if constexpr (L == 64) {
@@ -319,6 +316,7 @@ constexpr int kK3Block = 1024;
 constexpr int kK3Cap = 16384;  // candidates held in LDS (128 KiB); larger pools are read again
 constexpr int kK3Count = 128;  // pools up to this size are ranked by direct counting
 constexpr int kK3Waves = kK3Block / 64;
+constexpr int kK23Parts = 10240;  // the most partials that k23_small sums (40 KiB in LDS)
 
 // The k-th largest value (Top_maxO's threshold) by a radix select: 11 bits per
 // pass, starting at the highest bit in which value - smallest differs, which
@@ -696,37 +694,76 @@ __global__ __launch_bounds__(kK3Block) void k3_select(SelectArgs a) {
   if (tid == 0) finish_step(a, t_now, tot);
 }
 
-// K2 and K3 in one workgroup, for small workloads: at most kK3Block units,
-// each summed by one thread exactly as k2_update<1> sums it (or given its
-// norm), and the selection of K3 with every thread's candidate in its own
-// registers.  One launch instead of two; the same arithmetic, so the same
-// results.  Nothing is stored before the end, so that no barrier waits for a
-// store.
-__global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s) {
+// K2 and K3 in one workgroup, for small workloads (single_launch_update_select).
+// L lanes sum a unit's partials exactly as in k2_update<L>: one thread straight
+// from memory, more of them from LDS, where the partials arrive all in flight at
+// once.  Then one thread per unit, with its candidate in its own registers.  One
+// launch instead of two; the same arithmetic, so the same results.
+template <int L>
+__global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s, int num_parts) {
   __shared__ SelectShared sh;
   __shared__ uint64_t s_counts[kK3Waves];
   __shared__ uint8_t s_out[kK3Block];
-  const int b = int(threadIdx.x);
+  __shared__ int32_t s_off[kK3Block + 1];
+  __shared__ double s_ss[kK3Block];
+  __shared__ double red[kK3Waves];
+  __shared__ float s_part[kK23Parts];
+  const int b = int(threadIdx.x), l = b & 63, wave = __builtin_amdgcn_readfirstlane(b >> 6);
   const int64_t t_now = *s.step + 1;
-  sh.hist[2 * b] = sh.hist[2 * b + 1] = 0;
-  if (b == 0) sh.n = 0;
-  s_out[b] = 0;
   const bool has = b < u.num_units;
+  double n = 0.0;
+  if (L == 1) {
+    if (has)
+      n = u.ext_norm != nullptr
+              ? u.ext_norm[b]
+              : norm_of_sumsq(unit_ss<1>(u.unit_item_off, u.partial, b, 0, nullptr));
+    sh.hist[2 * b] = sh.hist[2 * b + 1] = 0;
+    if (b == 0) sh.n = 0;
+    s_out[b] = 0;
+  } else {
+    for (int i = 64 * wave; i < num_parts; i += kK3Block)
+      if (i + l < num_parts) load_to_lds(u.partial + i + l, s_part + i);
+    if (has) s_off[b + 1] = int32_t(u.unit_item_off[b + 1]);
+    if (b == 0) s_off[0] = 0;
+    sh.hist[2 * b] = sh.hist[2 * b + 1] = 0;
+    if (b == 0) sh.n = 0;
+    s_out[b] = 0;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    {
+      constexpr int kAtOnce = kK3Block / L;
+      for (int first = 0; first < u.num_units; first += kAtOnce) {
+        const int x = first + b / L;
+        const bool in = x < u.num_units;
+        const double w = wave_sum(
+            in ? lane_ss<L, int32_t>(s_part, s_off[x] + b % L, s_off[x + 1]) : 0.0);
+        if constexpr (L == 64) {
+          if (in && l == 0) s_ss[x] = w;
+        } else {
+          if (l == 0) red[wave] = w;
+          __syncthreads();
+          if (in && b % L == 0)
+            s_ss[x] = ((red[wave] + red[wave + 1]) + red[wave + 2]) + red[wave + 3];
+          __syncthreads();
+        }
+      }
+      __syncthreads();
+      if (has) n = norm_of_sumsq(s_ss[b]);
+    }
+  }
   UnitStep x{};
   if (has) {
-    const double n = u.ext_norm != nullptr
-                         ? u.ext_norm[b]
-                         : norm_of_sumsq(unit_ss<1>(u.unit_item_off, u.partial, b, 0, nullptr));
     x = update_unit(u, b, n);
+    store_unit(u, b, x);
   }
   const uint64_t mine = wave_counts(has, x);
   if ((b & 63) == 0) s_counts[b >> 6] = mine;
   __syncthreads();
-  int32_t tot[6] = {};
+  const uint64_t of_wave = s_counts[l & 15];  // each row of lanes sums over the waves
+  int32_t tot[6];
 #pragma unroll
-  for (int w = 0; w < kK3Waves; ++w)
-#pragma unroll
-    for (int k = 0; k < 6; ++k) tot[k] += count_of(s_counts[w], k);
+  for (int k = 0; k < 6; ++k)
+    tot[k] = int32_t(lane_of(row_prefix(uint32_t(count_of(of_wave, k))), 15));
   bool active = has && x.cand;
   uint32_t lo = ~0u, hi = 0;
   const uint32_t rank = rank_of(x.key);  // (0 for other than ranked candidates)
@@ -740,7 +777,6 @@ __global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s
   if (has) {
     u.mask[b] = active ? 1 : 0;
     u.lock[b] = active ? x.lock : 0;
-    store_unit(u, b, x);
   }
   if (b == 0) finish_step(s, t_now, tot);
 }
@@ -799,13 +835,29 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether one workgroup does the whole step: a unit by one thread, up to one per
+// thread and kK23Parts partials read; by a wavefront or a workgroup's worth of
+// lanes, while at most two rounds of 16 or 4 units follow each other.  One launch
+// against two, back to back (us): 28 units x 2 partials 3.9, 6.9; 1000 x 5 4.9,
+// 6.9; 7 x 691 5.1, 7.0; 1 x 256 3.9, 7.0; but 1000 x 31 8.7, 6.8; 84 x 73 7.0,
+// 7.0; 32 x 1000 12, 6.8.
 bool single_launch_update_select(const UpdateArgs& a, int64_t num_items) {
-  return a.num_units <= kK3Block &&
-         (a.ext_norm != nullptr || lanes_per_unit(num_items, a.num_units) == 1);
+  if (a.ext_norm != nullptr) return a.num_units <= kK3Block;
+  const int L = lanes_per_unit(num_items, a.num_units);
+  return num_items <= kK23Parts &&
+         a.num_units <= (L == 1 ? kK3Block : L == 64 ? 2 * kK3Waves : 2 * kK3Waves / 4);
 }
 
-hipError_t launch_update_select(const UpdateArgs& u, const SelectArgs& s, hipStream_t st) {
-  hipLaunchKernelGGL(k23_small, dim3(1), dim3(kK3Block), 0, st, u, s);
+hipError_t launch_update_select(const UpdateArgs& u, const SelectArgs& s, int64_t num_items,
+                                hipStream_t st) {
+  const int L = u.ext_norm != nullptr ? 1 : lanes_per_unit(num_items, u.num_units);
+  const int n = u.ext_norm != nullptr ? 0 : int(num_items);
+  if (L == 1)
+    hipLaunchKernelGGL(k23_small<1>, dim3(1), dim3(kK3Block), 0, st, u, s, n);
+  else if (L == 64)
+    hipLaunchKernelGGL(k23_small<64>, dim3(1), dim3(kK3Block), 0, st, u, s, n);
+  else
+    hipLaunchKernelGGL(k23_small<256>, dim3(1), dim3(kK3Block), 0, st, u, s, n);
   return hipGetLastError();
 }
 

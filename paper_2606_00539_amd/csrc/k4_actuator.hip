@@ -31,6 +31,7 @@
 #include <algorithm>
 
 #include "gnmr_internal.h"
+#include "lane_ops.h"
 
 namespace gnmr {
 namespace {
@@ -152,8 +153,7 @@ __device__ __forceinline__ void actuate_row(const ActSeg sg, int64_t row, bool v
     m = max_abs_pair(v[k].z, m);
     m = max_abs_pair(v[k].w, m);
   }
-#pragma unroll
-  for (int d = LANES > 64 ? 32 : LANES / 2; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+  m = lanes_max<(LANES > 64 ? 64 : LANES)>(m);
   float amax = m;
   if constexpr (LANES > 64) {
     if ((lane & 63) == 0) red[lane >> 6] = m;

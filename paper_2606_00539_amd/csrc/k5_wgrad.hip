@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "gnmr_internal.h"
+#include "lane_ops.h"
 
 namespace gnmr {
 namespace {
@@ -158,8 +159,7 @@ __device__ __forceinline__ void add_squares(const u32x2& p, float& ss) {
 // The sum over a wave's lanes (a butterfly) to red[wave], for the first four
 // waves of the workgroup.
 __device__ __forceinline__ void wave_sum_to(float ss, float* red, int tid) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) ss += __shfl_xor(ss, d, 64);
+  ss = wave_sum(ss);
   if ((tid & 63) == 0 && tid < kWgThreads) red[tid >> 6] = ss;
 }
 

@@ -90,3 +90,37 @@ def test_few_candidates_among_many_workgroups(U):
                 ctl.step_from_partials(torch.from_numpy(part).to("cuda"), 1.1, 1.5)
                 ref = ora.step(np.sqrt(scale * scale * parts), 1.1, 1.5)
                 assert_step_matches(ctl.query(), ref, rtol=1e-14, what=f"parts={parts} t={t}")
+
+
+@pytest.mark.parametrize("U,parts", [(1, 1), (1024, 10), (1024, 11), (1025, 1), (32, 320),
+                                     (32, 321), (33, 100), (8, 1280), (8, 1281), (9, 600),
+                                     (1, 10240), (1, 10241)])
+def test_one_and_two_launch_steps(U, parts):
+    """Around the limits of the single-workgroup step from partials: a unit by
+    one thread, a wavefront and a workgroup, in one launch and in two.  Units
+    of differing sizes, random partials: norms within float64 rounding of the
+    sums in another order, decisions the oracle's."""
+    torch = require_gpu()
+    from paper_2606_00539_amd import Controller
+
+    print(f"step from partials U={U} parts={parts}", flush=True)
+    rng = np.random.default_rng(U * 7 + parts)
+    sizes = np.full(U, parts)
+    if U > 1:                      # the same total: one unit gives, another takes
+        sizes[0] -= parts // 3
+        sizes[-1] += parts // 3
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    max_o = max(1, U // 4)
+    ora = Oracle(U, window=5, max_o=max_o, lock_len=2, eps=1e-12)
+    with Controller(U, 5, max_o, 2, 1e-12, np.zeros(U + 1, np.int64), [], []) as ctl:
+        ctl.bind_partials(off)
+        for t in range(1, 9):
+            scale = np.where(rng.random(U) < (0.5 if t == 7 else 0.0), 30.0 + 10 * rng.random(U),
+                             1.0)
+            part = ((0.999 + 0.002 * rng.random(int(off[-1]))) *
+                    np.repeat(scale, sizes)).astype(np.float32)
+            ctl.step_from_partials(torch.from_numpy(part).to("cuda"), 1.1, 1.5)
+            sums = [part[off[b]:off[b + 1]].astype(np.float64).sum() for b in range(U)]
+            ref = ora.step(np.sqrt(np.array(sums)), 1.1, 1.5)
+            # float64 sums of up to 10,241 positive terms in two orders: 2 n 2^-53
+            assert_step_matches(ctl.query(), ref, rtol=1e-11, what=f"t={t}")
