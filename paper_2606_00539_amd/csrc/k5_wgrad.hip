@@ -220,22 +220,27 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
     xr = __builtin_amdgcn_make_buffer_rsrc((void*)(x + kb * N), 0, rws * N * 2, kBufferWord3);
     yr = __builtin_amdgcn_make_buffer_rsrc((void*)(dy + kb * M), 0, rws * M * 2, kBufferWord3);
   };
-  auto gload = [&](int a, int h) {  // half h of both operands' chunks
+  constexpr int kPairs = 2 * kChunks;
+  // A step is staged in kPairs pairs p = 2 * chunk + operand (0: x, 1: dy).
+  auto gload = [&](int a, int lo, int hi) {
 #pragma unroll
-    for (int c = kChunks / 2 * h; c < kChunks / 2 * (h + 1); ++c) {
-      rx[a][c] = __builtin_bit_cast(
-          u32x4,
-          __builtin_amdgcn_raw_buffer_load_b128(xr, xo + uint32_t(c * 2 * kPass * N), 0, 0));
-      ry[a][c] = __builtin_bit_cast(
-          u32x4,
-          __builtin_amdgcn_raw_buffer_load_b128(yr, yo + uint32_t(c * 2 * kPass * M), 0, 0));
+    for (int p = lo; p < hi; ++p) {
+      const int c = p >> 1;
+      if ((p & 1) == 0)
+        rx[a][c] = __builtin_bit_cast(
+            u32x4,
+            __builtin_amdgcn_raw_buffer_load_b128(xr, xo + uint32_t(c * 2 * kPass * N), 0, 0));
+      else
+        ry[a][c] = __builtin_bit_cast(
+            u32x4,
+            __builtin_amdgcn_raw_buffer_load_b128(yr, yo + uint32_t(c * 2 * kPass * M), 0, 0));
     }
   };
-  auto lstore = [&](int buf, int a, int h) {
+  auto lstore = [&](int buf, int a, int lo, int hi) {
 #pragma unroll
-    for (int c = kChunks / 2 * h; c < kChunks / 2 * (h + 1); ++c) {
-      *(u32x4*)&lds[buf][0][(lrow + kPass * c) * kRow + lcol] = rx[a][c];
-      *(u32x4*)&lds[buf][1][(lrow + kPass * c) * kRow + lcol] = ry[a][c];
+    for (int p = lo; p < hi; ++p) {
+      const int c = p >> 1;
+      *(u32x4*)&lds[buf][p & 1][(lrow + kPass * c) * kRow + lcol] = p & 1 ? ry[a][c] : rx[a][c];
     }
   };
 
@@ -275,53 +280,54 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
   if constexpr (kT >= 128) {
     // Instruction order inside a slot (scheduling hints only): each
     // matrix-core instruction is followed by two fragment reads for the next
-    // slot and, in slots 0 and 1, by one LDS store and one global load (the
+    // slot and, where pairs are staged, by one LDS store and one global load (the
     // 256 tile has matrix-core instructions enough to give these their own).
     auto order = [](auto stores) {
-      constexpr bool kStores = decltype(stores)::value;
+      constexpr int kStores = decltype(stores)::value;
+      if constexpr (kT == 128) {
 #pragma unroll
-      for (int i = 0; i < 2 * kB; ++i) {
-        if constexpr (kT == 128) {
+        for (int i = 0; i < 4; ++i) {
           if (i % 2 == 0) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
           __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
-          if constexpr (kStores) {
+          if constexpr (kStores > 0) {
             __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
             __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
           }
-        } else {
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
           __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
           __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
         }
-      }
-      if constexpr (kT == 256) {
-        if constexpr (kStores) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
-          }
-        } else {
-          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8, 0);
+        for (int i = 0; i < kStores; ++i) {
+          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
         }
+        if constexpr (kStores < 8) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8 - kStores, 0);
       }
     };
-    const std::true_type with_stores;
-    const std::false_type without_stores;
+    // Pairs staged by the end of slots 0, 1 and 2.  In 256 tiles a slot's 16
+    // matrix-core instructions take 512 cycles of a CU and its 16 reads and 8
+    // stores per wave 529 cycles of LDS, so 8/8/0 pairs left the first two slots
+    // waiting for LDS; 6/5/5 fit all three.  The gradients of a layer (d = 5,120)
+    // at 2,048 tokens: 2,133 us at 8/8/0, 2,087 us at 6/5/5 (2,091-2,094 us at
+    // 6/6/4, 5/5/6 and 4/6/6).
+    constexpr int kCut0 = kT == 256 ? 6 : kPairs / 2, kCut1 = kT == 256 ? 11 : kPairs;
+    using std::integral_constant;
 
     // Prologue: step 0 in buffer 0, steps 1 .. kAhead in the staging
     // registers (step s in set s % kAhead), the first slot's fragments read.
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) {
       rsrc(int64_t(a) * kWgBK);
-      gload(a, 0);
-      gload(a, 1);
+      gload(a, 0, kPairs);
     }
-    lstore(0, 0, 0);
-    lstore(0, 0, 1);
+    lstore(0, 0, 0, kPairs);
     rsrc(int64_t(kAhead) * kWgBK);
-    gload(0, 0);
-    gload(0, 1);
+    gload(0, 0, kPairs);
     __syncthreads();
     rfrag(0, 0, 0);
     for (int64_t s0 = 0; s0 < nk; s0 += kAhead) {
@@ -330,23 +336,25 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
         const int64_t s = s0 + u;
         if (u > 0 && s >= nk) break;
         const int buf = kAhead > 1 ? u & 1 : int(s & 1), a = (u + 1) % kAhead;
-        // slot 0: stage half of step s+1, load half of step s+1+kAhead
+        // slot 0: stage part of step s+1, load the same part of step s+1+kAhead
         rfrag(1, buf, 1);
-        lstore(buf ^ 1, a, 0);
+        lstore(buf ^ 1, a, 0, kCut0);
         rsrc((s + 1 + kAhead) * kWgBK);
-        gload(a, 0);
+        gload(a, 0, kCut0);
         mfma(0);
-        order(with_stores);
-        // slot 1: the other halves
+        order(integral_constant<int, kCut0>{});
+        // slot 1
         rfrag(0, buf, 2);
-        lstore(buf ^ 1, a, 1);
-        gload(a, 1);
+        lstore(buf ^ 1, a, kCut0, kCut1);
+        gload(a, kCut0, kCut1);
         mfma(1);
-        order(with_stores);
+        order(integral_constant<int, kCut1 - kCut0>{});
         // slot 2
         rfrag(1, buf, 3);
+        lstore(buf ^ 1, a, kCut1, kPairs);
+        gload(a, kCut1, kPairs);
         mfma(0);
-        order(without_stores);
+        order(integral_constant<int, kPairs - kCut1>{});
         // slot 3: every wave has stored its part of step s+1 and read its last
         // fragments of buffer s%2 (the barrier waits for both), so buffer
         // (s+1)%2 is complete and buffer s%2 free for step s+2
@@ -355,7 +363,7 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
         __builtin_amdgcn_sched_barrier(0);
         rfrag(0, buf ^ 1, 0);
         mfma(1);
-        order(without_stores);
+        order(integral_constant<int, 0>{});
       }
     }
   } else {
@@ -365,14 +373,11 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) {
       rsrc(int64_t(a) * kWgBK);
-      gload(a, 0);
-      gload(a, 1);
+      gload(a, 0, kPairs);
     }
-    lstore(0, 0, 0);
-    lstore(0, 0, 1);
+    lstore(0, 0, 0, kPairs);
     rsrc(int64_t(kAhead) * kWgBK);
-    gload(0, 0);
-    gload(0, 1);
+    gload(0, 0, kPairs);
     for (int64_t s0 = 0; s0 < nk; s0 += kAhead) {
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
@@ -384,11 +389,9 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
         __syncthreads();
 #pragma unroll
         for (int kk = 0; kk < kSets; ++kk) rfrag(kk, buf, kk);
-        lstore(buf ^ 1, a, 0);
-        lstore(buf ^ 1, a, 1);
+        lstore(buf ^ 1, a, 0, kPairs);
         rsrc((s + 1 + kAhead) * kWgBK);
-        gload(a, 0);
-        gload(a, 1);
+        gload(a, 0, kPairs);
 #pragma unroll
         for (int kk = 0; kk < kSets; ++kk) mfma(kk);
       }
