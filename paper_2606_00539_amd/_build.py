@@ -1,9 +1,10 @@
-"""Builds libgnmr.so in-tree with hipcc for gfx950."""
+"""Builds libgnmr.so (hipcc for gfx950) and the module _calls (gcc) in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -13,6 +14,10 @@ SOURCES = [os.path.join(PKG, "csrc", f)
                      "k5_wgrad.hip")]
 HEADERS = [os.path.join(PKG, "csrc", f) for f in ("gnmr_internal.h", "k1_geometry.h", "lane_ops.h")] + [
     os.path.join(ROOT, "include", "gnmr.h")]
+
+# Marshalling of the per-step calls for Python (host code).
+CALLS = os.path.join(PKG, "_calls.so")
+CALLS_SOURCE = os.path.join(PKG, "csrc", "py_calls.c")
 
 # Packed-fp32 instructions are switched off for all device code.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
@@ -31,7 +36,18 @@ def build(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose: bool = True) -> str:
+    cmd = ["gcc", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], "-o", CALLS + ".tmp", CALLS_SOURCE]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(CALLS + ".tmp", CALLS)
+    return CALLS
 
 
 # AddressSanitizer and UndefinedBehaviorSanitizer on the host code only (the

@@ -1,4 +1,4 @@
-"""ctypes binding of libgnmr (include/gnmr.h): argument marshalling only.
+"""Binding of libgnmr (include/gnmr.h): argument marshalling only.
 
 Every computation of the controller pass runs in the HIP library.  Device
 pointers are plain ints (``tensor.data_ptr()``); streams are hipStream_t
@@ -79,11 +79,12 @@ class gnmr_stats(ctypes.Structure):
 
 
 _lib = None
+_calls = None
 
 
 def load_library(path: str = _LIB_PATH) -> ctypes.CDLL:
     """Load libgnmr.so (once).  Raises if it is not built."""
-    global _lib
+    global _lib, _calls
     if _lib is not None and path == _LIB_PATH:
         return _lib
     if not os.path.exists(path):
@@ -124,8 +125,34 @@ def load_library(path: str = _LIB_PATH) -> ctypes.CDLL:
     lib.gnmr_last_error.argtypes = []
     lib.gnmr_last_error.restype = ctypes.c_char_p
     if path == _LIB_PATH:
+        _calls = _load_calls(lib)
         _lib = lib
     return lib
+
+
+# The entry points of a training step are called through csrc/py_calls.c: ctypes and
+# Python marshalled for longer than the small calls' kernels run.  All others stay
+# with ctypes.
+_PER_STEP = ("gnmr_step", "gnmr_step_from_norms", "gnmr_step_from_partials", "gnmr_sumsq",
+             "gnmr_actuate", "gnmr_actuate_matrix", "gnmr_wgrad_sumsq",
+             "gnmr_wgrad_sumsq_batched")
+
+
+def _load_calls(lib):
+    """The module of the per-step calls, set to the functions of `lib`."""
+    try:
+        from . import _calls as calls
+    except ImportError as e:
+        raise RuntimeError(f"the module _calls is not built; run __graft_entry__.build() first "
+                           f"({e})") from e
+    calls.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _PER_STEP})
+    return calls
+
+
+def _native():
+    if _calls is None:
+        load_library()
+    return _calls
 
 
 def _check(status: int) -> None:
@@ -172,23 +199,15 @@ def gnmr_destroy(ctx) -> None:
 
 
 def gnmr_step(ctx, alpha_t, beta_t, seg_ptr=None, stream=None) -> None:
-    ptrs = None if seg_ptr is None else _ptr_array(seg_ptr)
-    _check(load_library().gnmr_step(ctx, float(alpha_t), float(beta_t),
-                                    None if ptrs is None else ctypes.cast(ptrs, ctypes.c_void_p),
-                                    _stream(stream)))
+    _check(_native().step(ctx, alpha_t, beta_t, seg_ptr, stream))
 
 
 def gnmr_step_from_norms(ctx, d_norm, alpha_t, beta_t, stream=None) -> None:
-    p = d_norm.data_ptr() if hasattr(d_norm, "data_ptr") else int(d_norm)
-    _check(load_library().gnmr_step_from_norms(ctx, p, float(alpha_t), float(beta_t),
-                                               _stream(stream)))
+    _check(_native().step_from_norms(ctx, d_norm, alpha_t, beta_t, stream))
 
 
 def gnmr_sumsq(ctx, d_sumsq, seg_ptr=None, stream=None) -> None:
-    ptrs = None if seg_ptr is None else _ptr_array(seg_ptr)
-    p = d_sumsq.data_ptr() if hasattr(d_sumsq, "data_ptr") else int(d_sumsq)
-    _check(load_library().gnmr_sumsq(ctx, None if ptrs is None else ctypes.cast(ptrs, ctypes.c_void_p),
-                                     p, _stream(stream)))
+    _check(_native().sumsq(ctx, seg_ptr, d_sumsq, stream))
 
 
 def gnmr_sumsq_noalloc(num_units, unit_seg_off, seg_numel, seg_dtype, seg_ptr, d_sumsq,
@@ -214,23 +233,14 @@ def gnmr_wgrad_num_tiles(out_features, in_features) -> int:
 
 def gnmr_wgrad_sumsq(dy, x, dw, tokens, out_features, in_features, tile_sumsq,
                      stream=None) -> None:
-    _check(load_library().gnmr_wgrad_sumsq(_dptr(dy), _dptr(x), _dptr(dw), int(tokens),
-                                           int(out_features), int(in_features),
-                                           _dptr(tile_sumsq), _stream(stream)))
+    _check(_native().wgrad_sumsq(dy, x, dw, tokens, out_features, in_features, tile_sumsq,
+                                 stream))
 
 
 def gnmr_wgrad_sumsq_batched(problems, tile_sumsq, stream=None) -> None:
     """problems: iterable of (dy, x, dw, tokens, out_features, in_features)
     or (dy, x, dw, tokens, out_features, in_features, accumulate)."""
-    ps = []
-    for p in problems:
-        a, b, c, t, o, i = p[:6]
-        acc = int(p[6]) if len(p) > 6 else 0
-        ps.append(gnmr_wgrad_problem(_dptr(a), _dptr(b), _dptr(c), int(t), int(o), int(i), acc,
-                                     0))
-    arr = (gnmr_wgrad_problem * max(len(ps), 1))(*ps)
-    _check(load_library().gnmr_wgrad_sumsq_batched(arr, len(ps), _dptr(tile_sumsq),
-                                                   _stream(stream)))
+    _check(_native().wgrad_sumsq_batched(problems, tile_sumsq, stream))
 
 
 def gnmr_bind_partials(ctx, unit_part_off) -> None:
@@ -239,8 +249,7 @@ def gnmr_bind_partials(ctx, unit_part_off) -> None:
 
 
 def gnmr_step_from_partials(ctx, d_partial, alpha_t, beta_t, stream=None) -> None:
-    _check(load_library().gnmr_step_from_partials(ctx, _dptr(d_partial), float(alpha_t),
-                                                  float(beta_t), _stream(stream)))
+    _check(_native().step_from_partials(ctx, d_partial, alpha_t, beta_t, stream))
 
 
 def gnmr_query(ctx, num_units, stream=None) -> dict:
@@ -321,15 +330,13 @@ def gnmr_actuator_create(segments, num_units, stream=None) -> ctypes.c_void_p:
 
 
 def gnmr_actuate(act, d_mask, fmt_low, fmt_recovery, stream=None) -> None:
-    p = d_mask.data_ptr() if hasattr(d_mask, "data_ptr") else int(d_mask)
-    _check(load_library().gnmr_actuate(act, p, int(fmt_low), int(fmt_recovery), _stream(stream)))
+    _check(_native().actuate(act, d_mask, fmt_low, fmt_recovery, stream))
 
 
 def gnmr_actuate_matrix(x, out, rows, cols, d_mask, unit, fmt_low, fmt_recovery,
                         stream=None) -> None:
-    _check(load_library().gnmr_actuate_matrix(_dptr(x), _dptr(out), int(rows), int(cols),
-                                              _dptr(d_mask), int(unit), int(fmt_low),
-                                              int(fmt_recovery), _stream(stream)))
+    _check(_native().actuate_matrix(x, out, rows, cols, d_mask, unit, fmt_low, fmt_recovery,
+                                    stream))
 
 
 def gnmr_actuator_info(act) -> dict:
