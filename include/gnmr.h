@@ -283,7 +283,8 @@ gnmr_status gnmr_get_state(gnmr_ctx* ctx, void* buf, size_t bytes, void* stream)
 gnmr_status gnmr_set_state(gnmr_ctx* ctx, const void* buf, size_t bytes, void* stream);
 
 /* Kernel timing.  While enabled, every step records HIP events around each of
- * its kernels on its stream.  gnmr_profile_read waits for them and returns the
+ * its kernels on its stream, which then have launches of their own also where
+ * they would otherwise share one.  gnmr_profile_read waits for them and returns the
  * summed milliseconds of the gradient pass, the state update and the
  * selection kernels over the steps recorded since enabling, and that number of
  * steps; any output may be NULL.  Enabling resets the sums. */
@@ -292,7 +293,9 @@ gnmr_status gnmr_profile_read(gnmr_ctx* ctx, double* ms_sumsq, double* ms_update
                               double* ms_select, int64_t* steps);
 
 /* Work-list facts: K1 work items, bytes per item, gradient bytes per step and
- * kernel launches per gnmr_step.  Any output may be NULL. */
+ * the kernels that a gnmr_step is made of, each a launch while profiling (up to
+ * 256 units of up to 6,144 items in all: one launch for all of them otherwise).
+ * Any output may be NULL. */
 gnmr_status gnmr_info(const gnmr_ctx* ctx, int64_t* num_items, int64_t* item_bytes,
                       int64_t* bytes_per_step, int32_t* launches_per_step);
 

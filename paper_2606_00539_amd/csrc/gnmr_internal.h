@@ -130,6 +130,16 @@ constexpr int kK1FewPassed = 64, kK1MostPassed = 448;
 hipError_t launch_sumsq(const Item* items, int64_t num_items, const char** seg_base,
                         const void* const* ptrs, int64_t num_segs, const int32_t* seg_dtype,
                         float* partial, hipStream_t s);
+// K1, K2 and K3 as one launch (k123_step.hip).  words: [num_items] and launches: [1],
+// zero before the first launch and used by nothing else.
+constexpr int64_t kStepItems = 6144;
+bool whole_step_in_one_launch(int32_t num_units, int64_t num_items);
+// Lanes that sum one unit's partials.
+int lanes_per_unit(int64_t num_items, int32_t num_units);
+hipError_t launch_step(const Item* items, int64_t num_items, const char** seg_base,
+                       const void* const* ptrs, int64_t num_segs, const int32_t* seg_dtype,
+                       uint64_t* words, uint32_t* launches, const UpdateArgs& u,
+                       const SelectArgs& s, hipStream_t st);
 hipError_t launch_unit_sumsq(const int64_t* unit_item_off, const float* partial,
                              int64_t num_items, int32_t num_units, double* out, hipStream_t s);
 hipError_t launch_update(const UpdateArgs& a, int64_t num_items, SelectArgs* sel, hipStream_t s);

@@ -165,6 +165,8 @@ struct gnmr_ctx {
   double* d_gsum = nullptr;
   gnmr_stats* d_stats = nullptr;
   int64_t* d_step = nullptr;   // steps completed (advanced by K3)
+  uint64_t* d_words = nullptr;     // [num_items] if the step is one launch (k123_step.hip)
+  uint32_t* d_launches = nullptr;  // and the number of those launches
 
   // partial sums of squares made by a producer (gnmr_bind_partials)
   int64_t* d_ext_off = nullptr;  // [U+1]
@@ -302,12 +304,11 @@ gnmr_status record(gnmr_ctx* c, int which, hipStream_t st) {
   return GNMR_OK;
 }
 
-// K2 + K3 for step t+1 over the partial sums `partial` ([num_parts], unit b
-// owning [off[b], off[b+1])), or over the norms ext_norm when it is non-null.
-gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* partial,
-                              const int64_t* off, int64_t num_parts, double alpha, double beta,
-                              hipStream_t st) {
-  gnmr::UpdateArgs u{};
+// The arguments of K2 and K3 for the next step over the partial sums `partial`
+// (unit b owning [off[b], off[b+1])), or over the norms ext_norm when non-null.
+void control_args(const gnmr_ctx* c, const double* ext_norm, const float* partial,
+                  const int64_t* off, double alpha, double beta, gnmr::UpdateArgs& u,
+                  gnmr::SelectArgs& s) {
   u.num_units = c->U;
   u.window = c->window;
   u.admitted = c->budget_mode == GNMR_BUDGET_ADMITTED ? 1 : 0;
@@ -335,7 +336,6 @@ gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* 
   u.pool_unit = c->d_pool_unit;
   u.key_low = c->d_key_low;
   u.wg_counts = c->d_wg_counts;
-  gnmr::SelectArgs s{};
   s.max_o = c->max_o;
   s.warmup = c->warmup_steps;
   s.step = c->d_step;
@@ -346,6 +346,15 @@ gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* 
   s.lock = c->d_lock;
   s.mask = c->d_mask;
   s.stats = c->d_stats;
+}
+
+// K2 + K3 for step t+1 over num_parts partial sums or the norms.
+gnmr_status update_and_select(gnmr_ctx* c, const double* ext_norm, const float* partial,
+                              const int64_t* off, int64_t num_parts, double alpha, double beta,
+                              hipStream_t st) {
+  gnmr::UpdateArgs u{};
+  gnmr::SelectArgs s{};
+  control_args(c, ext_norm, partial, off, alpha, beta, u, s);
   gnmr_status r = GNMR_OK;
   if (gnmr::single_launch_update_select(u, num_parts)) {
     // small workload: K2 + K3 in one launch (timed as the update; select 0)
@@ -466,6 +475,10 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   const size_t o_gsum = take(size_t(U) * sizeof(double));
   const size_t o_st = take(sizeof(gnmr_stats));
   const size_t o_step = take(sizeof(int64_t));
+  const bool one_launch = gnmr::whole_step_in_one_launch(int32_t(U), int64_t(items.size()));
+  const size_t words_bytes = one_launch ? items.size() * sizeof(uint64_t) : 0;
+  const size_t o_words = take(words_bytes);
+  const size_t o_launches = take(sizeof(uint32_t));
   const size_t total = off;
 
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -500,6 +513,8 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   c->d_gsum = reinterpret_cast<double*>(base + o_gsum);
   c->d_stats = reinterpret_cast<gnmr_stats*>(base + o_st);
   c->d_step = reinterpret_cast<int64_t*>(base + o_step);
+  if (one_launch) c->d_words = reinterpret_cast<uint64_t*>(base + o_words);
+  c->d_launches = reinterpret_cast<uint32_t*>(base + o_launches);
 
   if (hipHostMalloc(reinterpret_cast<void**>(&c->h_ptr_stage),
                     std::max<size_t>(size_t(S), 1) * sizeof(void*), hipHostMallocDefault) !=
@@ -536,6 +551,8 @@ gnmr_status gnmr_init(gnmr_ctx** out, const gnmr_config* cfg, const gnmr_segment
   if (e == hipSuccess) e = hipMemsetAsync(c->d_gsum, 0, size_t(U) * sizeof(double), st);
   if (e == hipSuccess) e = hipMemsetAsync(c->d_stats, 0, sizeof(gnmr_stats), st);
   if (e == hipSuccess) e = hipMemsetAsync(c->d_step, 0, sizeof(int64_t), st);
+  if (e == hipSuccess && one_launch) e = hipMemsetAsync(c->d_words, 0, words_bytes, st);
+  if (e == hipSuccess) e = hipMemsetAsync(c->d_launches, 0, sizeof(uint32_t), st);
   if (e == hipSuccess && S > 0)
     e = hipMemsetAsync(c->d_seg_base, 0, size_t(S) * sizeof(void*), st);
   // wait for what was enqueued also on failure: the uploads read host vectors
@@ -575,6 +592,15 @@ gnmr_status gnmr_step(gnmr_ctx* ctx, double alpha_t, double beta_t, const void* 
   const void* const* passed = nullptr;
   r = bind_ptrs(ctx, seg_ptr, st, &passed);
   if (r != GNMR_OK) return r;
+  // (the profile tells K1's time from K2's, so it takes launches of their own)
+  if (ctx->d_words != nullptr && !ctx->prof) {
+    gnmr::UpdateArgs u{};
+    gnmr::SelectArgs s{};
+    control_args(ctx, nullptr, nullptr, ctx->d_unit_item_off, alpha_t, beta_t, u, s);
+    GNMR_HIP(gnmr::launch_step(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
+                               ctx->d_seg_dtype, ctx->d_words, ctx->d_launches, u, s, st));
+    return GNMR_OK;
+  }
   r = record(ctx, 0, st);
   if (r != GNMR_OK) return r;
   GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,

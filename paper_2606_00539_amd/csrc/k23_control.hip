@@ -15,57 +15,10 @@
 
 #include "gnmr_internal.h"
 #include "lane_ops.h"
+#include "unit_step.h"
 
 namespace gnmr {
 namespace {
-
-// Scans and reductions of 32-bit values over a wavefront by data-parallel
-// primitives: four shifts inside the rows of 16 lanes, then the rows' last
-// lanes passed on (about 50 cycles, where six dependent lane permutes through
-// LDS take several hundred).
-template <typename Op>
-__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
-  auto step = [&](auto ctrl, auto rows) {
-    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
-                                                   decltype(rows)::value, 0xF, false)));
-  };
-  constexpr int kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
-  using std::integral_constant;
-  step(integral_constant<int, kShr + 1>{}, integral_constant<int, 0xF>{});
-  step(integral_constant<int, kShr + 2>{}, integral_constant<int, 0xF>{});
-  step(integral_constant<int, kShr + 4>{}, integral_constant<int, 0xF>{});
-  step(integral_constant<int, kShr + 8>{}, integral_constant<int, 0xF>{});
-  step(integral_constant<int, kBcast15>{}, integral_constant<int, 0xA>{});
-  step(integral_constant<int, kBcast31>{}, integral_constant<int, 0xC>{});
-  return x;
-}
-
-// Inclusive prefix sum over the lanes; the last lane holds the total.
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
-  return wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-}
-
-// The same inside each row of 16 lanes.
-template <typename Op>
-__device__ __forceinline__ uint32_t row_scan(uint32_t x, uint32_t identity, Op op) {
-  auto step = [&](auto ctrl) {
-    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
-                                                   0xF, 0xF, false)));
-  };
-  step(std::integral_constant<int, 0x111>{});
-  step(std::integral_constant<int, 0x112>{});
-  step(std::integral_constant<int, 0x114>{});
-  step(std::integral_constant<int, 0x118>{});
-  return x;
-}
-
-__device__ __forceinline__ uint32_t row_prefix(uint32_t x) {
-  return row_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-}
-
-__device__ __forceinline__ uint32_t lane_of(uint32_t x, int lane) {
-  return uint32_t(__builtin_amdgcn_readlane(int(x), lane));
-}
 
 struct Min {
   __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
@@ -73,24 +26,6 @@ struct Min {
 struct Max {
   __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
 };
-
-// Fixed-order float64 sum of unit b's item partials by L lanes (lane < L):
-// each lane keeps four running sums over a stride-L walk, then the lanes are
-// combined by a fixed butterfly (L = 64) and a fixed cross-wave order
-// (L = 256).  L = 1 is one thread per unit, for units of few items.
-template <int L, typename Index>
-__device__ __forceinline__ double lane_ss(const float* partial, Index i, Index hi) {
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  for (; i + 3 * L < hi; i += 4 * L) {
-    const float a = partial[i], c = partial[i + L], d = partial[i + 2 * L], e = partial[i + 3 * L];
-    s0 += double(a);
-    s1 += double(c);
-    s2 += double(d);
-    s3 += double(e);
-  }
-  for (; i < hi; i += L) s0 += double(partial[i]);
-  return (s0 + s1) + (s2 + s3);
-}
 
 template <int L>
 __device__ __forceinline__ double unit_ss(const int64_t* __restrict__ off,
@@ -122,146 +57,6 @@ __global__ __launch_bounds__(256) void k_unit_sumsq(const int64_t* __restrict__ 
   if (lane == 0) out[b] = s;
 }
 
-// n_{b,t} from a unit's float64 sum of squares.  The sums of squares are
-// accumulated in fp32, whose range ends at 2^128: a unit whose sum reaches it
-// (a gradient norm of 2^64 or more) has no representable fp32 sum, so its
-// norm is taken as +inf, a non-finite norm (the outcome when an fp32 square
-// or partial overflows, made independent of how the sum is split into items).
-// NaN stays NaN.
-__device__ __forceinline__ double norm_of_sumsq(double ss) {
-  return ss >= 0x1p128 ? double(INFINITY) : sqrt(ss);
-}
-
-// Order-preserving key of a candidate: R >= 0 (or +inf), so its IEEE bits
-// are monotone in R; +1 keeps 0 free for "not a candidate".
-__device__ __forceinline__ uint64_t cand_key(double R) {
-  return uint64_t(__double_as_longlong(R)) + 1;
-}
-
-// A candidate's place in the ranking to 32 bits: the key's upper half and one
-// more, 0 for a unit that is active without ranking (key 0).  Units that are
-// equal here are told apart by the key's lower half.
-__device__ __forceinline__ uint32_t rank_of(uint64_t key) {
-  return key != 0 ? uint32_t(key >> 32) + 1u : 0u;
-}
-
-// One unit's step: what is stored for it, and its part in the counters and the
-// candidate pool.
-struct UnitStep {
-  double n, A, G, D, R, gsum;
-  uint64_t key;   // candidates: the ranking key, 0 when active without ranking
-  int32_t lock;   // Lock after the step if the unit is selected
-  int32_t slot;   // ring slot of the new GNMR
-  bool cand, tg, td, tr, finite;
-};
-
-// Alg. 1 and the risk of Alg. 2 for unit b given its norm n, and the unit's
-// membership of the candidate pool C_t.  Stores nothing.
-__device__ __forceinline__ UnitStep update_unit(const UpdateArgs& a, int b, double n) {
-  const int U = a.num_units;
-  // The step counter lives on the device, so that a captured step replays
-  // correctly: t = 1 + steps completed, the queue holds min(t - 1, delta)
-  // values, and the oldest value sits in the slot the new one replaces.
-  const int64_t t = *a.step + 1;
-  const int qlen = t - 1 < a.window ? int(t - 1) : a.window;
-  const int slot0 = int((t - 1) % a.window);
-  const bool warm = t <= a.warmup;
-  const bool finite = isfinite(n);
-  const double A_prev = a.A[b];
-  // Alg. 1: GNMR = 1 at t = 1 or while the historical mean is 0.
-  double G = 1.0;
-  if (finite && t > 1 && A_prev != 0.0) G = n / (A_prev + a.eps);
-  // Alg. 1: Delta-GNMR once the queue holds delta values, oldest first.
-  double D = 1.0;
-  if (qlen == a.window) {
-    double total = 0.0;
-    int slot = slot0;
-    for (int j = 0; j < a.window; ++j) {
-      total += a.Q[int64_t(slot) * U + b];
-      slot = slot + 1 == a.window ? 0 : slot + 1;
-    }
-    const double den = total / double(a.window) + a.eps;
-    if (finite && den != 0.0) D = G / den;
-  }
-  // Alg. 1: running mean (and, in store_unit, the queue push: the new value
-  // replaces the oldest).
-  UnitStep u{};
-  u.n = n;
-  u.A = finite ? A_prev + (n - A_prev) / double(t) : A_prev;
-  u.slot = slot0;
-  u.finite = finite;
-  if (!finite) G = D = INFINITY;
-  u.G = G;
-  u.D = D;
-
-  // Alg. 2: R = max(GNMR / alpha, Delta-GNMR / beta); the pool C_t holds the
-  // recoverable units with R > 1 or a lock left from the previous step.
-  const double gt = G / a.alpha;
-  const double dt = D / a.beta;
-  const double R = gt > dt ? gt : dt;
-  u.R = R;
-  const bool rec = a.rec[b] != 0;
-  const bool trig = R > 1.0;
-  const int32_t prev_lock = a.lock[b];
-  const bool prev_active = a.mask[b] != 0;
-  bool cand = rec && (trig || prev_lock > 0);
-  bool keep = false;
-  double rank_by = R;
-  if (a.static_set) {                 // static baseline: profile, rank once, hold
-    u.gsum = a.gsum[b];
-    if (t <= a.warmup) {
-      u.gsum += finite ? G : 0.0;
-      cand = keep = rec;
-    } else if (t == a.warmup + 1) {
-      cand = rec;
-      rank_by = u.gsum / double(a.warmup);   // mean GNMR over steps 1..W
-    } else {
-      cand = keep = prev_active;
-    }
-  } else if (warm) {                  // warm-up: C_t = A_t = B_rec
-    cand = rec;
-    keep = rec;
-  } else if (a.admitted && cand) {    // admitted-only budget: A_{t-1} members stay
-    keep = prev_active;
-  }
-  u.key = cand && !keep ? cand_key(rank_by) : 0;
-  u.lock = trig ? a.lock_len : (prev_lock > 0 ? prev_lock - 1 : 0);
-  u.cand = cand;
-  u.tg = rec && gt > 1.0;
-  u.td = rec && dt > 1.0;
-  u.tr = rec && trig;
-  return u;
-}
-
-// Everything of the step but the selection's outcome.
-__device__ __forceinline__ void store_unit(const UpdateArgs& a, int b, const UnitStep& u) {
-  a.A[b] = u.A;
-  a.Q[int64_t(u.slot) * a.num_units + b] = u.finite ? u.G : 1.0;
-  if (a.static_set) a.gsum[b] = u.gsum;
-  a.norm[b] = u.n;
-  a.gnmr[b] = u.G;
-  a.dgnmr[b] = u.D;
-  a.risk[b] = u.R;
-}
-
-// The counters' contributions of one wavefront, kCountBits bits each: at most
-// 256 units per workgroup, so the sum over a workgroup's waves fits too.
-constexpr int kCountBits = 10;
-enum : int { kCntCand, kCntRank, kCntTrigG, kCntTrigD, kCntTrigR, kCntNonFinite };
-
-__device__ __forceinline__ int32_t count_of(uint64_t packed, int which) {
-  return int32_t(packed >> (which * kCountBits)) & ((1 << kCountBits) - 1);
-}
-
-__device__ __forceinline__ uint64_t wave_counts(bool has, const UnitStep& u) {
-  auto count = [&](bool x, int which) {
-    return uint64_t(__popcll(__ballot(has && x))) << (which * kCountBits);
-  };
-  return count(u.cand, kCntCand) | count(u.cand && u.key != 0, kCntRank) |
-         count(u.tg, kCntTrigG) | count(u.td, kCntTrigD) | count(u.tr, kCntTrigR) |
-         count(!u.finite, kCntNonFinite);
-}
-
 // K2: L lanes per unit sum its partials; lane 0 then runs Alg. 1, the risk of
 // Alg. 2, and marks the unit's membership of the candidate pool C_t.  Each
 // workgroup leaves its counts in one word and its members of C_t at the start
@@ -289,7 +84,7 @@ __global__ __launch_bounds__(256) void k2_update(UpdateArgs a) {
   }
   const bool has = in && lane == 0;
   UnitStep u{};
-  if (has) u = update_unit(a, b, n);
+  if (has) u = update_unit(a, past_of_unit(a, b), n);
   const uint64_t members = __ballot(has && u.cand);
   uint64_t mine = wave_counts(has, u);
   int at = __popcll(members & ((uint64_t(1) << (tid & 63)) - 1));
@@ -575,26 +370,6 @@ __device__ __forceinline__ void widen_range(uint32_t rank, uint32_t& lo, uint32_
   hi = rank > hi ? rank : hi;
 }
 
-// The counters of step t, by thread 0.
-__device__ __forceinline__ void finish_step(const SelectArgs& a, int64_t t,
-                                            const int32_t (&tot)[6]) {
-  const int32_t n_cand = tot[kCntCand], n_rank = tot[kCntRank];
-  const bool warm = t <= a.warmup;
-  gnmr_stats st;
-  st.t = t;
-  st.n_trig_gnmr = tot[kCntTrigG];
-  st.n_trig_dgnmr = tot[kCntTrigD];
-  st.n_trig = tot[kCntTrigR];
-  st.n_cand = n_cand;
-  // the kept units, and as many ranked ones as the budget takes
-  st.n_active = n_cand - n_rank + (n_rank < a.max_o ? n_rank : a.max_o);
-  st.hit_maxo = (!warm && n_rank > 0 && n_rank >= a.max_o) ? 1 : 0;
-  st.n_nonfinite = tot[kCntNonFinite];
-  st.reserved = 0;
-  *a.stats = st;
-  *a.step = t;
-}
-
 // K3: a single workgroup, over the members of C_t that K2's workgroups left.
 // When the budget takes them all it only adds up the counters.  Bound by
 // latency: one load for the counts, one batch of loads for the pool (ranks and
@@ -753,7 +528,7 @@ __global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s
   }
   UnitStep x{};
   if (has) {
-    x = update_unit(u, b, n);
+    x = update_unit(u, past_of_unit(u, b), n);
     store_unit(u, b, x);
   }
   const uint64_t mine = wave_counts(has, x);
@@ -786,7 +561,7 @@ __global__ __launch_bounds__(kK3Block) void k23_small(UpdateArgs u, SelectArgs s
 // Lanes per unit for the partial sums: one thread when units have few items,
 // a wavefront for moderate counts, a whole workgroup once long strided walks
 // would be latency bound.
-static int lanes_per_unit(int64_t num_items, int32_t num_units) {
+int lanes_per_unit(int64_t num_items, int32_t num_units) {
   const int64_t per = num_items / (num_units > 0 ? num_units : 1);
   return per < 32 ? 1 : per < 512 ? 64 : 256;
 }

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace gnmr {
 
 // op(x of this lane, x of lane ^ kMask) for a symmetric op, kMask 32, 16, 8, 4,
@@ -84,6 +86,54 @@ __device__ __forceinline__ float lanes_max(float v) {
   x = with_other<2>(x, larger);
   x = with_other<1>(x, larger);
   return __uint_as_float(x);
+}
+
+// Scans and reductions of 32-bit values over a wavefront by data-parallel
+// primitives: four shifts inside the rows of 16 lanes, then the rows' last
+// lanes passed on (about 50 cycles, where six dependent lane permutes through
+// LDS take several hundred).
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
+  auto step = [&](auto ctrl, auto rows) {
+    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xF, false)));
+  };
+  constexpr int kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+  using std::integral_constant;
+  step(integral_constant<int, kShr + 1>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 2>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 4>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kShr + 8>{}, integral_constant<int, 0xF>{});
+  step(integral_constant<int, kBcast15>{}, integral_constant<int, 0xA>{});
+  step(integral_constant<int, kBcast31>{}, integral_constant<int, 0xC>{});
+  return x;
+}
+
+// Inclusive prefix sum over the lanes; the last lane holds the total.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  return wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+// The same inside each row of 16 lanes.
+template <typename Op>
+__device__ __forceinline__ uint32_t row_scan(uint32_t x, uint32_t identity, Op op) {
+  auto step = [&](auto ctrl) {
+    x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(identity), int(x), decltype(ctrl)::value,
+                                                   0xF, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{});
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  return x;
+}
+
+__device__ __forceinline__ uint32_t row_prefix(uint32_t x) {
+  return row_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+__device__ __forceinline__ uint32_t lane_of(uint32_t x, int lane) {
+  return uint32_t(__builtin_amdgcn_readlane(int(x), lane));
 }
 
 }  // namespace gnmr

@@ -1,0 +1,70 @@
+"""A small workload's step in one launch gives the bits of the step whose kernels
+are launched one by one (which profiling asks for), up to and past its limits."""
+import numpy as np
+import pytest
+
+from gpu_util import require_gpu
+from paper_2606_00539_amd import GNMR_BF16, GNMR_F32, Controller
+
+pytestmark = pytest.mark.gpu
+ITEM = 65536  # bytes
+FIELDS = ("mask", "lock", "norm", "gnmr", "dgnmr", "risk")
+
+
+def sizes_of(units, items, dtype):
+    """Values per unit: `items` work items in all, shared as evenly as they go,
+    the last of each unit ragged (an empty unit where a share is 0)."""
+    per = ITEM // (2 if dtype == GNMR_BF16 else 4)
+    share = [items // units + (b < items % units) for b in range(units)]
+    return [n * per - (37 * b + 5) % 1000 if n else 0 for b, n in enumerate(share)]
+
+
+# (units, items): one lane, a wavefront or a workgroup's order per unit; around
+# 1,024 items (the late ones), 256 units and 6,144 items
+@pytest.mark.parametrize("units,items,dtype", [
+    (1, 1, GNMR_F32), (1, 33, GNMR_BF16), (28, 196, GNMR_F32), (3, 1023, GNMR_BF16),
+    (30, 1024, GNMR_BF16), (33, 1057, GNMR_BF16), (84, 6048, GNMR_BF16), (256, 100, GNMR_F32),
+    (256, 6144, GNMR_BF16), (192, 6144, GNMR_BF16), (7, 6144, GNMR_BF16), (1, 6144, GNMR_BF16),
+    (257, 300, GNMR_F32), (100, 6145, GNMR_BF16)])
+@pytest.mark.parametrize("passed", [False, True])
+def test_one_launch_gives_the_bits_of_several(units, items, dtype, passed):
+    torch = require_gpu()
+    print("one launch", units, items, dtype, passed, flush=True)
+    sizes = sizes_of(units, items, dtype)
+    g = torch.Generator(device="cuda").manual_seed(units * 10007 + items)
+    flat = torch.empty(sum(sizes) + 8 * units, device="cuda",
+                       dtype=torch.bfloat16 if dtype == GNMR_BF16 else torch.float32)
+    segs, at = [], 0
+    for b, n in enumerate(sizes):   # addresses that are not multiples of 16
+        segs.append(flat[at:at + n])
+        at += n + b % 8
+    off = np.arange(units + 1)
+    cfg = dict(window=3, max_o=max(1, units // 8), lock_len=2, eps=1e-12)
+    args = (off, sizes, [dtype] * units, None if passed else segs)
+    rng = np.random.default_rng(units + items)
+    with Controller(units, *cfg.values(), *args) as one, \
+            Controller(units, *cfg.values(), *args) as ref:
+        assert one.info()["num_items"] == items
+        ref.set_profiling(True)
+        for t in range(1, 7):
+            flat.normal_(0.0, 1e-3, generator=g)
+            for b in rng.choice(units, max(1, units // 4), replace=False):
+                segs[b].mul_(float(rng.uniform(2, 20)))
+            if t == 5:
+                segs[0].fill_(float("inf"))
+            for c in (one, ref):
+                c.step(1.1, 1.3, seg_ptr=segs if passed else None)
+            a, b = one.query(), ref.query()
+            for k in FIELDS:
+                assert a[k].tobytes() == b[k].tobytes(), (t, k)
+            assert a["stats"] == b["stats"] and a["stats"]["t"] == t
+            if t == 3:   # a state taken back: the same step number again
+                saved = one.get_state()
+            if t == 4:
+                one.set_state(saved)
+                ref.set_state(saved)
+                for c in (one, ref):
+                    c.step(1.1, 1.3, seg_ptr=segs if passed else None)
+                a, b = one.query(), ref.query()
+                assert all(a[k].tobytes() == b[k].tobytes() for k in FIELDS)
+                assert a["stats"]["t"] == 4
