@@ -278,10 +278,15 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
   };
   const int64_t nk = (K + kWgBK - 1) / kWgBK;  // 0 steps for an empty batch: dw = 0
   if constexpr (kT >= 128) {
-    // Instruction order inside a slot (scheduling hints only): each
-    // matrix-core instruction is followed by two fragment reads for the next
-    // slot and, where pairs are staged, by one LDS store and one global load (the
-    // 256 tile has matrix-core instructions enough to give these their own).
+    // Instruction order inside a slot (scheduling hints only).  128 tile: two
+    // fragment reads for the next slot behind each matrix-core instruction and,
+    // where pairs are staged, one LDS store and one global load.  256 tile: the
+    // reads first, three to a matrix-core instruction, then a pair's store and
+    // load behind every second one: with one wave per SIMD a store that finds the
+    // LDS queue full holds up the matrix cores.  4096^3 and the gradients of a
+    // layer (d = 5,120, 4,096 tokens): 112.6 and 2,167 us; two reads each, then a
+    // pair behind each of the next: 114.8 and 2,195; reads and stores mixed over
+    // the slot: 118 to 121 and 2,370 to 2,470.
     auto order = [](auto stores) {
       constexpr int kStores = decltype(stores)::value;
       if constexpr (kT == 128) {
@@ -296,24 +301,27 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 5; ++i) {
           __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 3, 0);
         }
+        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
 #pragma unroll
-        for (int i = 0; i < kStores; ++i) {
-          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
+        for (int i = 0; i < 6; ++i) {
+          if (i < kStores) {
+            __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
+          }
+          if (i < 5) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
         }
-        if constexpr (kStores < 8) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 8 - kStores, 0);
       }
     };
     // Pairs staged by the end of slots 0, 1 and 2.  In 256 tiles a slot's 16
     // matrix-core instructions take 512 cycles of a CU and its 16 reads and 8
     // stores per wave 529 cycles of LDS, so 8/8/0 pairs left the first two slots
     // waiting for LDS; 6/5/5 fit all three.  The gradients of a layer (d = 5,120)
-    // at 2,048 tokens: 2,133 us at 8/8/0, 2,087 us at 6/5/5 (2,091-2,094 us at
+    // at 4,096 tokens: 2,133 us at 8/8/0, 2,087 us at 6/5/5 (2,091-2,094 us at
     // 6/6/4, 5/5/6 and 4/6/6).
     constexpr int kCut0 = kT == 256 ? 6 : kPairs / 2, kCut1 = kT == 256 ? 11 : kPairs;
     using std::integral_constant;
