@@ -278,23 +278,27 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
   };
   const int64_t nk = (K + kWgBK - 1) / kWgBK;  // 0 steps for an empty batch: dw = 0
   if constexpr (kT >= 128) {
-    // Instruction order inside a slot (scheduling hints only).  128 tile: two
-    // fragment reads for the next slot behind each matrix-core instruction and,
-    // where pairs are staged, one LDS store and one global load.  256 tile: the
-    // reads first, three to a matrix-core instruction, then a pair's store and
-    // load behind every second one: with one wave per SIMD a store that finds the
-    // LDS queue full holds up the matrix cores.  4096^3 and the gradients of a
-    // layer (d = 5,120, 4,096 tokens): 112.6 and 2,167 us; two reads each, then a
-    // pair behind each of the next: 114.8 and 2,195; reads and stores mixed over
-    // the slot: 118 to 121 and 2,370 to 2,470.
+    // Instruction order inside a slot (scheduling hints only): the fragment reads
+    // for the next slot first, three to a matrix-core instruction (four in the 128
+    // tile), then the staged pairs' stores and loads, spaced out.  A wave that
+    // finds the LDS queue full holds up the matrix cores, with one wave per SIMD.
+    // 256 tile, 4096^3 and the gradients of a layer (d = 5,120, 4,096 tokens):
+    // 112.6 and 2,167 us; two reads each, then a pair behind each of the next:
+    // 114.8 and 2,195; reads and stores mixed over the slot: 118 to 121 and 2,370
+    // to 2,470.  128 tile, 1024 x 2048 and 2048 x 2048 gradients of 8,192 and 4,096
+    // tokens: 66.6 and 44.8 us, mixed and in two slots 75.0 and 47.1.
     auto order = [](auto stores) {
       constexpr int kStores = decltype(stores)::value;
       if constexpr (kT == 128) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (i % 2 == 0) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
-          if constexpr (kStores > 0) {
+        for (int i = 0; i < 2; ++i) {
+          __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          if (i < 2) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+          if (i < kStores) {
             __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
             __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
           }
@@ -322,8 +326,8 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
     // stores per wave 529 cycles of LDS, so 8/8/0 pairs left the first two slots
     // waiting for LDS; 6/5/5 fit all three.  The gradients of a layer (d = 5,120)
     // at 4,096 tokens: 2,133 us at 8/8/0, 2,087 us at 6/5/5 (2,091-2,094 us at
-    // 6/6/4, 5/5/6 and 4/6/6).
-    constexpr int kCut0 = kT == 256 ? 6 : kPairs / 2, kCut1 = kT == 256 ? 11 : kPairs;
+    // 6/6/4, 5/5/6 and 4/6/6).  The 128 tile's eight pairs: 3/3/2.
+    constexpr int kCut0 = kT == 256 ? 6 : 3, kCut1 = kT == 256 ? 11 : 6;
     using std::integral_constant;
 
     // Prologue: step 0 in buffer 0, steps 1 .. kAhead in the staging
