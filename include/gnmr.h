@@ -341,7 +341,8 @@ typedef struct gnmr_actuator gnmr_actuator;
  * for the tables (8 B per row, 24 B per segment).  At most 67,108,860 rows of
  * up to 4096 features and 16,777,215 longer rows in all; GNMR_E_INVALID
  * beyond.  A call launches one kernel per class of row widths present (at most
- * 12). */
+ * 12), or, with up to 64 MB of input, one for all rows of up to 8192 features
+ * and one per wider class. */
 gnmr_status gnmr_actuator_create(gnmr_actuator** out, const gnmr_act_segment* segs,
                                  int64_t num_segments, int32_t num_units, void* stream);
 

@@ -260,6 +260,51 @@ void for_class(int cls, const F& f) {
   else if constexpr (kClass + 1 < kK4Classes) for_class<kClass + 1>(cls, f);
 }
 
+// The classes whose workgroups have kK4Block lanes.
+constexpr int kMixed = 10;
+static_assert(block_of(kClasses[kMixed - 1].lanes) == kK4Block &&
+              block_of(kClasses[kMixed].lanes) > kK4Block, "");
+
+// Rows of several classes in one launch: workgroups [block[c], block[c + 1]) take
+// rows [row[c], row[c + 1]) of the table.
+struct MixedRows {
+  uint32_t block[kMixed + 1], row[kMixed + 1];
+};
+
+template <int kClass = 0>
+__device__ __forceinline__ void mixed_row(int cls, uint32_t w, const MixedRows& rows,
+                                          const RowItem* items, const ActSeg* segs,
+                                          const uint8_t* mask, int fmt_low, int fmt_rec,
+                                          float* red) {
+  if (cls == kClass) {
+    constexpr int kLanes = kClasses[kClass].lanes;
+    const uint32_t sub = kLanes < kK4Block ? threadIdx.x / kLanes : 0;
+    // (each class over all XCDs: its workgroups have less or more to do than others)
+    const uint32_t at =
+        xcd_order(w - rows.block[kClass], rows.block[kClass + 1] - rows.block[kClass]);
+    const uint32_t r = rows.row[kClass] + at * (kK4Block / kLanes) + sub;
+    const bool valid = r < rows.row[kClass + 1];
+    const RowItem it = items[valid ? r : rows.row[kClass + 1] - 1];
+    const ActSeg sg = segs[it.seg];
+    __builtin_amdgcn_sched_barrier(0);
+    actuate_row<kLanes, kClasses[kClass].vpt, true, kLanes >= 64>(
+        sg, it.row, valid, mask, fmt_low, fmt_rec, int(threadIdx.x) % kLanes, red);
+  } else if constexpr (kClass + 1 < kMixed) {
+    mixed_row<kClass + 1>(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
+  }
+}
+
+__global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 6))) void k4_mixed(
+    const RowItem* __restrict__ items, const MixedRows rows, const ActSeg* __restrict__ segs,
+    const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
+  __shared__ float red[kK4Block / 64];
+  const uint32_t w = blockIdx.x;
+  int cls = 0;
+#pragma unroll
+  for (int c = 1; c < kMixed; ++c) cls = w >= rows.block[c] ? c : cls;
+  mixed_row(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
+}
+
 struct TableLaunch {
   const RowItem* items;
   int64_t rows;
@@ -321,10 +366,32 @@ int k4_class(int cols) {
   return c;
 }
 
+// Tables small enough for cached loads take one launch for all classes present but
+// the two of 512 lanes, where a launch per class takes 1.5 to 4 us more: the inputs
+// of layers' projections, two widths, per class and in one launch, 8.1 and 4.1 us
+// (2.8 MB), 10.1 and 6.4 (8.1 MB), 14.0 and 11.7 (22.5 MB), 26.1 and 23.6 (61 MB).
+// (All rows by the widest class's kernel: 5.0, 7.6 and 18.4 of the first three.)
 hipError_t launch_actuate(const RowItem* items, const int64_t* class_off, int64_t bytes,
                           const ActSeg* segs, const uint8_t* mask, int fmt_low, int fmt_rec,
                           hipStream_t s) {
-  for (int c = 0; c < kK4Classes; ++c)
+  int first = 0, present = 0;
+  for (int c = 0; c < kMixed; ++c) present += class_off[c + 1] > class_off[c] ? 1 : 0;
+  if (present > 1 && bytes <= kK4CachedBytes) {
+    MixedRows m{};
+    uint32_t blocks = 0;
+    for (int c = 0; c < kMixed; ++c) {
+      const int64_t per = kK4Block / kClasses[c].lanes, n = class_off[c + 1] - class_off[c];
+      m.block[c] = blocks;
+      m.row[c] = uint32_t(class_off[c]);
+      blocks += uint32_t((n + per - 1) / per);
+    }
+    m.block[kMixed] = blocks;
+    m.row[kMixed] = uint32_t(class_off[kMixed]);
+    hipLaunchKernelGGL(k4_mixed, dim3(blocks), dim3(kK4Block), 0, s, items, m, segs, mask, fmt_low,
+                       fmt_rec);
+    first = kMixed;
+  }
+  for (int c = first; c < kK4Classes; ++c)
     if (class_off[c + 1] > class_off[c])
       for_class(c, TableLaunch{items + class_off[c], class_off[c + 1] - class_off[c], segs, mask,
                                fmt_low, fmt_rec, bytes <= kK4CachedBytes, s});

@@ -91,3 +91,34 @@ def test_large_matrix_equals_its_parts(rows, cols):
     gnmr_actuate_matrix(x[half:], parts[half:], rows - half, cols, mask, 0, LOW, REC)
     torch.cuda.synchronize()
     assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
+
+
+# one launch for the classes of up to 256 lanes with up to 64 MB of input, a launch
+# per class beyond; rows that fill their class's workgroups and rows that do not
+@pytest.mark.parametrize("rows", [1, 8, 33])
+@pytest.mark.parametrize("widths", [(8, 136), (1024, 2312), (128, 3080, 16384), tuple(WIDTHS)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_classes_of_a_small_table_in_one_launch(rows, widths, past):
+    torch = require_gpu()
+    from paper_2606_00539_amd import Actuator
+
+    print(f"actuator mixed {rows} {widths} {past}", flush=True)
+    rng = np.random.default_rng(rows + len(widths))
+    acts = [rows_of(rng, rows, c) for c in widths]
+    U = len(acts) + 1
+    fill = ((64 << 20) - sum(a.size * 2 for a in acts)) // 2048 + past
+    filler = torch.zeros((fill, 1024), dtype=torch.int16, device="cuda")
+    mask = (np.arange(U) % 2).astype(np.uint8)
+    d_in = [to_device(torch, a) for a in acts]
+    d_out = [torch.full_like(t, 0x5555) for t in d_in]
+    segs = [(i, o, rows, a.shape[1], b) for b, (i, o, a) in enumerate(zip(d_in, d_out, acts))]
+    for few in (False, True):
+        for o in d_out:
+            o.fill_(0x5555)
+        with Actuator(segs + ([] if few else [(filler, filler, fill, 1024, U - 1)]), U) as act:
+            act.apply(torch.from_numpy(mask).to("cuda"), LOW, 3)
+            torch.cuda.synchronize()
+        for o, w in zip(d_out, FQ.actuate(acts, mask[:-1], LOW, 3)):
+            got = o.cpu().numpy().view(np.uint16).reshape(w.shape)
+            assert np.array_equal(got, w), f"cols {w.shape[1]}"
+    assert not filler.any()
