@@ -23,7 +23,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 # the sources of the gradient-pass kernel whose HBM counters profiles/ records
-K1_SOURCES = ("k1_sumsq.hip", "k1_geometry.h")
+K1_SOURCES = ("k1_sumsq.hip", "k1_item.h", "k1_geometry.h")
 METRIC = "GNMR step GB/s (frac. of HBM peak) + µs/step, 13B-shaped grads, 1 GPU"
 # below this many gradient bytes per step the step is launch-bound, and the
 # per-kernel events stay out of the timed steps

@@ -37,8 +37,8 @@
 // 256x256 tiles.  Every tile size accumulates over k in the same order, and the
 // squares are added in the same order, so the results have the same bits.
 // The 28 gradients of a 4-layer, d = 256 model at 2,037 tokens (52 tiles of 256):
-// 98 us in 256 tiles (two launches of at most 16 problems), 37 us in 208 tiles
-// of 128 (one launch of at most 32, 26 us, and the sums, 6 us).
+// 93 us in 256 tiles (two launches of at most 16 problems), 26 us in 208 tiles
+// of 128 (one launch of at most 32, 21 us, and the sums, 5 us).
 
 #include <type_traits>
 
@@ -583,16 +583,16 @@ void launch_tiled(const WgBatch& batch, int acc, hipStream_t s) {
 }
 
 // The tile edge for one launch.  A 256 tile does the most work per LDS byte
-// and writes its own sum, but takes 8.5 us plus 1.1 us per K step of 64
+// and writes its own sum, but takes 7.5 us plus 1.0 us per K step of 64
 // however few of the 256 CUs have one; the smaller tiles add the k5_tile_sums
-// launch (about 6 us) and spread the same steps over 4 or 16 times the
+// launch (about 5 us) and spread the same steps over 4 or 16 times the
 // workgroups.  Measured on square problems, call to call, 256 / 128 / 64 tile:
-//   tokens 4096:  G = 1: 77 / 40 / 28 us    G = 16: 78 / 44 / 31
-//                 G = 64: 79 / 46 / 65      G = 121: 80 / 75 / 114
-//                 G = 144: 81 / 106 / 130   (G: number of 256 tiles)
-//   tokens 1024:  G = 1: 25 / 18 / 14       G = 64: 27 / 23 / 26
-//                 G = 100: 27 / 27 / 36
-//   tokens 256:   G = 16: 12.3 / 12.5 / 11  G = 64: 13 / 16 / 18
+//   tokens 4096:  G = 1: 71 / 37 / 28 us    G = 16: 72 / 38 / 30
+//                 G = 64: 73 / 46 / 65      G = 121: 74 / 77 / 118
+//                 G = 144: 77 / 101 / 135   (G: number of 256 tiles)
+//   tokens 1024:  G = 1: 23 / 16 / 13       G = 64: 26 / 21 / 24
+//                 G = 100: 26 / 26 / 35
+//   tokens 256:   G = 16: 11.9 / 11.6 / 10.1  G = 64: 13 / 15 / 17
 // So: the 64 tile while every CU gets at most one and there are 4 steps to
 // share; the 128 tile while every CU gets at most one and the steps outweigh
 // the second launch (4 plus one per 64 tiles more), or at most two and 32
