@@ -35,7 +35,8 @@ constexpr uint32_t kPolls = 1u << 28;
 
 // The last items by workgroup number, collected after everything else has been
 // done for the units whose items all came before them: about what is in flight
-// when the last workgroup starts.
+// when the last workgroup starts.  84 units in 6,048 items: 62.9 us a step; 512:
+// 64.9, 256: 65.7, 2,048: 62.9.
 constexpr uint32_t kLate = 1024;
 
 struct StepShared {
