@@ -167,7 +167,8 @@ __device__ __forceinline__ void wave_sum_to(float ss, float* red, int tid) {
 // overwrites it (false); a batch of both kinds takes one launch of each.
 // kT: the tile edge.  256 writes the tile sums itself; the smaller tiles leave
 // them to k5_tile_sums.
-template <bool kAcc, int kT>
+// kRows: accumulated tiles leave in full rows (rows_pay).
+template <bool kAcc, int kT, bool kRows = false>
 __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const WgBatch batch) {
   using G = Tile<kT>;
   constexpr int kB = G::kB, kW = G::kW, kRow = G::kRow, kChunks = G::kChunks, kPass = G::kPass;
@@ -452,14 +453,14 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
     tile_to_lds<kT, 4>(tile, dw, m0, n0, M, N, tid);
     __syncthreads();
   }
-  if (!kAcc && m0 + kT <= M && n0 + kT <= N) {
-    // Overwriting a tile wholly inside dw (uniform): the rounded tile goes
+  if ((!kAcc || kRows) && m0 + kT <= M && n0 + kT <= N) {
+    // A tile wholly inside dw (uniform): the rounded tile goes
     // to the free LDS buffers first, in the swizzled layout of the stored
     // tile, then leaves in full rows: each wavefront store covers whole rows
     // (1 KiB of them), where a lane's own accumulator layout would touch 32
-    // rows with 16 bytes each.  (Accumulating, the same staging spills
-    // registers in the 256 tile and measured no faster, so those tiles store
-    // directly.)
+    // rows with 16 bytes each.  Accumulating, it goes where the stored values
+    // were read.  (That spills eight registers in the 256 tile, so it is done
+    // only where it pays.)
 #pragma unroll
     for (int i = 0; i < kB; ++i) {
 #pragma unroll
@@ -571,10 +572,26 @@ WgBatch tiled(const WgBatch& batch, int acc) {
   return b;
 }
 
+// Whether accumulated tiles leave in full rows: where most of them have rows a
+// multiple of 4,096 bytes apart.  There a wavefront's store of 16 bytes to each of
+// 32 rows meets few memory channels: four 2048 x 2048 gradients, two 5504 x 2048
+// and one 2048 x 5504 of 64 and 1,024 tokens take 95 and 159 us stored directly
+// and 73 and 146 in rows, 4096 x 4096 of 64 and 4,096 tokens 24.2 and 121 against
+// 21.4 and 119.  Other strides are as fast directly, or up to 4% faster.
+bool rows_pay(const WgBatch& b) {
+  int64_t strided = 0;
+  for (int i = 0; i < b.num; ++i)
+    if (b.p[i].N % 2048 == 0) strided += int64_t(b.p[i].tiles_m) * b.p[i].tiles_n;
+  return 2 * strided > b.total_tiles;
+}
+
 template <int kT>
 void launch_tiled(const WgBatch& batch, int acc, hipStream_t s) {
   const WgBatch b = tiled<kT>(batch, acc);
-  if (acc)
+  if (acc && rows_pay(b))
+    hipLaunchKernelGGL((k5_wgrad<true, kT, true>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads),
+                       0, s, b);
+  else if (acc)
     hipLaunchKernelGGL((k5_wgrad<true, kT>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0, s,
                        b);
   else

@@ -71,6 +71,23 @@ def test_every_tile_size_gives_the_same_bits(M, N, T):
         np.testing.assert_allclose(a[1], W.tile_sumsq(a[0]), rtol=SS_RTOL, atol=0)
 
 
+# rows a multiple of 4,096 bytes apart, in 64, 128 and 256 tiles with ragged edges
+@pytest.mark.parametrize("M,N,T", [(264, 2048, 300), (776, 2048, 700), (2056, 4096, 64)])
+def test_accumulated_tiles_stored_in_rows(M, N, T):
+    """Alone, most tiles of the launch have such rows and are stored row by row;
+    with a filler whose rows are 6,144 bytes apart they are stored directly."""
+    torch = require_gpu()
+    print(f"wgrad rows M={M} N={N} T={T}", flush=True)
+    dy, x = SW.operands(5, 1, M + N, tokens=T, out_f=M, in_f=N)
+    old = W.bf16_rne(np.random.default_rng(M).standard_normal((M, N)) * 0.02)
+    (rows, ss), = launch(torch, [(dy, x, old, 1)], 0)
+    (direct, ss_direct), = launch(torch, [(dy, x, old, 1)], 3072)
+    assert np.array_equal(rows, direct) and np.array_equal(ss, ss_direct)
+    exact = W.wgrad_accumulate_exact(old, dy, x)
+    assert np.all(np.abs(W.widen_bf16(rows) - exact) <= W.error_bound_accumulate(old, dy, x, exact))
+    np.testing.assert_allclose(ss, W.tile_sumsq(rows), rtol=SS_RTOL, atol=0)
+
+
 def test_more_problems_than_one_launch_holds():
     """35 problems (a launch holds 32) of differing sizes and both kinds: every
     dw the oracle's bit for bit on integer operands, tile sums at the
