@@ -407,6 +407,18 @@ __global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const 
         gload(a, 0, kPairs);
 #pragma unroll
         for (int kk = 0; kk < kSets; ++kk) mfma(kk);
+        // Reads first, then a pair behind each matrix-core instruction (left to
+        // the compiler the stores mixed with the reads: 512 x 512 of 4,096 tokens
+        // 29.7 us, now 25.2; 1024 x 1024 of 8,192 51.1 and 42.4).
+        __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 12, 0);
+        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (i < 3) __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedDsWrite, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedVmemRead, 1, 0);
+        }
       }
     }
   }
@@ -604,16 +616,18 @@ void launch_tiled(const WgBatch& batch, int acc, hipStream_t s) {
 // however few of the 256 CUs have one; the smaller tiles add the k5_tile_sums
 // launch (about 5 us) and spread the same steps over 4 or 16 times the
 // workgroups.  Measured on square problems, call to call, 256 / 128 / 64 tile:
-//   tokens 4096:  G = 1: 71 / 37 / 28 us    G = 16: 72 / 38 / 30
-//                 G = 64: 73 / 46 / 65      G = 121: 74 / 77 / 118
+//   tokens 4096:  G = 1: 71 / 37 / 24 us    G = 16: 72 / 38 / 26
+//                 G = 25: 72 / 38 / 37      G = 36: 72 / 39 / 47
+//                 G = 64: 73 / 46 / 63      G = 121: 74 / 77 / 118
 //                 G = 144: 77 / 101 / 135   (G: number of 256 tiles)
-//   tokens 1024:  G = 1: 23 / 16 / 13       G = 64: 26 / 21 / 24
-//                 G = 100: 26 / 26 / 35
-//   tokens 256:   G = 16: 11.9 / 11.6 / 10.1  G = 64: 13 / 15 / 17
+//   tokens 1024:  G = 1: 23 / 16 / 13       G = 25: 24 / 18 / 17
+//                 G = 64: 25 / 21 / 24      G = 100: 26 / 26 / 35
+//   tokens 256:   G = 16: 11.9 / 12.9 / 11.2  G = 25: 12.3 / 13.2 / 13.0
+//                 G = 64: 13 / 15 / 17
 // So: the 64 tile while every CU gets at most one and there are 4 steps to
-// share; the 128 tile while every CU gets at most one and the steps outweigh
-// the second launch (4 plus one per 64 tiles more), or at most two and 32
-// steps; otherwise the 256 tile.
+// share, or at most two and 16 steps; the 128 tile while every CU gets at most
+// one and the steps outweigh the second launch (4 plus one per 64 tiles more),
+// or at most two and 32 steps; otherwise the 256 tile.
 int tile_edge(const WgBatch& batch, int acc) {
   const WgBatch b = tiled<64>(batch, acc);
   const int64_t n64 = b.total_tiles, n128 = tiled<128>(batch, acc).total_tiles;
@@ -621,6 +635,7 @@ int tile_edge(const WgBatch& batch, int acc) {
   for (int i = 0; i < b.num; ++i)
     steps = b.p[i].K > steps * kWgBK ? (b.p[i].K + kWgBK - 1) / kWgBK : steps;
   if (n64 <= 256 && steps >= 4) return 64;
+  if (n64 <= 512 && steps >= 16) return 64;
   if (n128 <= 256 && steps >= 4 + n128 / 64) return 128;
   if (n128 <= 512 && steps >= 32) return 128;
   return 256;

@@ -47,14 +47,14 @@ def launch(torch, problems, filler):
 # step of 64 and the staging rings of two and four steps
 @pytest.mark.parametrize("M,N,T", [(8, 8, 256), (64, 72, 257), (72, 64, 319), (128, 136, 320),
                                    (136, 264, 321), (256, 328, 449), (264, 520, 512),
-                                   (520, 248, 577)])
+                                   (520, 248, 577), (1160, 1096, 1025)])
 def test_every_tile_size_gives_the_same_bits(M, N, T):
     torch = require_gpu()
     print(f"wgrad tiles M={M} N={N} T={T}", flush=True)
     dy, x = SW.operands(3, 1, M + N, tokens=T, out_f=M, in_f=N)
     old = W.bf16_rne(np.random.default_rng(M * N).standard_normal((M, N)) * 0.02)
     problems = [(dy, x, old, 0), (dy, x, old, 1)]
-    small = launch(torch, problems, 0)          # 64: at most 256 workgroups
+    small = launch(torch, problems, 0)          # 64: at most 256 workgroups, 512 from 1,024 tokens
     medium = launch(torch, problems, 1280)      # 128: over 256 of 64, under 256 of 128
     large = launch(torch, problems, 3072)       # 256
     for (acc, a, b, c) in zip((0, 1), small, medium, large):
