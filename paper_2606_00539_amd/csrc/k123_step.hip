@@ -150,7 +150,9 @@ __device__ void control(const UpdateArgs& u, const SelectArgs& s, const uint64_t
   }
   int n_late = 0;
   if (lanes != 1) {
-    bool late = false;
+    // (all units where nothing is collected before the last items, those without any
+    // too: each unit is summed in one of the two passes, an empty one to 0)
+    bool late = has && late_from == 0;
     if (hi > lo) {
       const uint32_t last = item_wg(uint32_t(hi) - 1, num);
       late = last >= late_from || item_wg(uint32_t(lo), num) % kNumXcd != last % kNumXcd;

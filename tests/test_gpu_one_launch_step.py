@@ -68,3 +68,61 @@ def test_one_launch_gives_the_bits_of_several(units, items, dtype, passed):
                 a, b = one.query(), ref.query()
                 assert all(a[k].tobytes() == b[k].tobytes() for k in FIELDS)
                 assert a["stats"]["t"] == 4
+
+
+def uneven(counts, dtype, empty):
+    """CSR offsets and segment sizes of units of counts[b] work items, in up to two
+    segments; a unit of none has no segment, or (`empty`) two of no values."""
+    per = ITEM // (2 if dtype == GNMR_BF16 else 4)
+    off, sizes = [0], []
+    for b, n in enumerate(counts):
+        if n > 1:
+            sizes += [(n // 2) * per, (n - n // 2) * per - 3 * b - 1]
+        elif n or empty:
+            sizes += [per - 1] if n else [0, 0]
+        off.append(len(sizes))
+    return np.array(off, np.int64), sizes
+
+
+# Units without items first, in the middle and last, and units of very different
+# sizes: a wavefront's and a workgroup's order per unit, below, at and above the
+# 1,024 items that are all collected at once.
+@pytest.mark.parametrize("counts", [
+    [100, 0], [64, 0], [0, 400, 400], [40, 0, 100, 50], [1023, 0], [1024, 0], [1025, 0],
+    [512, 0, 512], [513, 0, 512], [2000, 0, 2000], [0] + [40] * 20, [40] * 10 + [0] + [40] * 10,
+    [40] * 20 + [0], [0, 0, 300, 0], [3, 900, 1, 100], [1, 2500, 0, 2, 1200, 60, 2],
+    [0] + [60, 3, 200, 0] * 12], ids=lambda c: f"{len(c)}u{sum(c)}i{c.index(0) if 0 in c else ''}")
+@pytest.mark.parametrize("empty", [False, True])
+@pytest.mark.parametrize("passed", [False, True])
+def test_units_without_items_and_uneven_units(counts, empty, passed):
+    torch = require_gpu()
+    from paper_2606_00539_amd import gnmr_wgrad_num_tiles, gnmr_wgrad_sumsq
+
+    print("uneven units", counts, empty, passed, flush=True)
+    U, none = len(counts), np.array(counts) == 0
+    off, sizes = uneven(counts, GNMR_BF16, empty)
+    g = torch.Generator(device="cuda").manual_seed(sum(counts))
+    flat = torch.empty(sum(sizes), device="cuda", dtype=torch.bfloat16)
+    segs, at = [], 0
+    for n in sizes:
+        segs.append(flat[at:at + n] if n else 0)
+        at += n
+    args = (off, sizes, [GNMR_BF16] * len(sizes), None if passed else segs)
+    # other kernels leave their operands in the compute units' LDS
+    dy = torch.randn(64, 4096, device="cuda", generator=g).bfloat16() + 3
+    dw = torch.empty(4096, 4096, device="cuda", dtype=torch.bfloat16)
+    sums = torch.empty(gnmr_wgrad_num_tiles(4096, 4096), device="cuda")
+    with Controller(U, 3, 1, 2, 1e-12, *args) as one, \
+            Controller(U, 3, 1, 2, 1e-12, *args) as ref:
+        assert one.info()["num_items"] == sum(counts)
+        ref.set_profiling(True)
+        for t in range(1, 6):
+            flat.normal_(0.0, 1e-3 * t, generator=g)
+            gnmr_wgrad_sumsq(dy, dy, dw, 64, 4096, 4096, sums)
+            for c in (one, ref):
+                c.step(1.1, 1.3, seg_ptr=segs if passed else None)
+            a, b = one.query(), ref.query()
+            assert np.all(a["norm"][none] == 0.0), (t, a["norm"][none])
+            for k in FIELDS:
+                assert a[k].tobytes() == b[k].tobytes(), (t, k)
+            assert a["stats"] == b["stats"]
