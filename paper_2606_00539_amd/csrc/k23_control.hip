@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "gnmr_internal.h"
+#include "k3_pool.h"
 #include "lane_ops.h"
 #include "unit_step.h"
 
@@ -344,14 +345,16 @@ struct GlobalPool {
   const uint32_t* pool_rank;
   const int32_t* pool_unit;
   const uint64_t* wg_counts;
-  int places, shift;
+  uint32_t places;
+  int shift;
   uint32_t lo, hi;
   template <typename F>
   __device__ __forceinline__ void each(F f) const {
-    for (int base = 0; base < places; base += kK3Block) {
-      const int i = base + int(threadIdx.x);
-      const bool valid =
-          i < places && (i & ((1 << shift) - 1)) < count_of(wg_counts[i >> shift], kCntCand);
+    const uint32_t rounds = pool_rounds(places, kK3Block);
+    for (uint32_t r = 0; r < rounds; ++r) {
+      const uint32_t i = r * kK3Block + threadIdx.x;
+      const bool valid = i < places && int32_t(i & ((1u << shift) - 1u)) <
+                                           count_of(wg_counts[i >> shift], kCntCand);
       f(valid ? pool_rank[i] : 0, valid ? pool_unit[i] : 0, valid);
     }
   }
@@ -459,7 +462,8 @@ __global__ __launch_bounds__(kK3Block) void k3_select(SelectArgs a) {
       pool.hi = hi;
       select_pool(pool, n_cand, tot[kCntRank], a.max_o, key_low, sh, drop);
     } else {
-      GlobalPool pool{a.pool_rank, a.pool_unit, a.wg_counts, a.num_wgs << a.wg_shift, a.wg_shift, 0, 0};
+      GlobalPool pool{a.pool_rank, a.pool_unit, a.wg_counts, pool_places(a.num_wgs, a.wg_shift),
+                      a.wg_shift, 0, 0};
       pool.each([&](uint32_t rank, int32_t, bool) { widen_range(rank, lo, hi); });
       pool.lo = lo;
       pool.hi = hi;
