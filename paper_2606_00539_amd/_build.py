@@ -14,7 +14,7 @@ SOURCES = [os.path.join(PKG, "csrc", f)
                      "k4_actuator.hip", "k5_wgrad.hip")]
 HEADERS = [os.path.join(PKG, "csrc", f)
            for f in ("gnmr_internal.h", "k1_geometry.h", "k1_item.h", "k3_pool.h", "lane_ops.h",
-                     "unit_step.h")] + [os.path.join(ROOT, "include", "gnmr.h")]
+                     "launch_tag.h", "unit_step.h")] + [os.path.join(ROOT, "include", "gnmr.h")]
 
 # Marshalling of the per-step calls for Python (host code).
 CALLS = os.path.join(PKG, "_calls.so")

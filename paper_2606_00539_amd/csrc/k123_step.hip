@@ -22,6 +22,7 @@
 
 #include "gnmr_internal.h"
 #include "k1_item.h"
+#include "launch_tag.h"
 #include "unit_step.h"
 
 namespace gnmr {
@@ -30,7 +31,8 @@ namespace {
 constexpr int kStepUnits = kK1Block;  // one thread per unit
 
 // About a microsecond each: minutes, against a step's microseconds.  A workload
-// whose items do not arrive by then ends with NaN norms, not in a hang.
+// whose items do not arrive by then ends with NaN norms, not in a hang; so do its
+// later steps, whose words could not be told from those still to come.
 constexpr uint32_t kPolls = 1u << 28;
 
 // The last items by workgroup number, collected after everything else has been
@@ -46,16 +48,19 @@ struct StepShared {
   int32_t off[kStepUnits + 1];
   int32_t unit[kStepUnits];   // units with late items first
   int32_t late[kK1Block / 64];
+  int32_t lost[kK1Block / 64];  // whether a word of the wave's has not arrived
 };
 
 // Waits for the words of workgroups [from, to); the partials go to part[item].
 __device__ __forceinline__ void collect(const uint64_t* words, uint32_t num, uint32_t from,
-                                        uint32_t to, uint32_t tag, float* part) {
+                                        uint32_t to, uint32_t tag, float* part, int32_t* lost) {
   constexpr int kAtOnce = 4;  // words in flight per lane
+  const uint32_t most = words_lost(tag) ? 1 : kPolls;
   for (uint32_t first = from + threadIdx.x; first < to; first += kAtOnce * kK1Block) {
     uint64_t v[kAtOnce];
+    uint32_t polls = 0;
 #pragma unroll 1
-    for (uint32_t polls = 0; polls < kPolls; ++polls) {
+    for (; polls < most; ++polls) {
       bool all = true;
 #pragma unroll
       for (int k = 0; k < kAtOnce; ++k) {
@@ -68,6 +73,7 @@ __device__ __forceinline__ void collect(const uint64_t* words, uint32_t num, uin
       if (all) break;
       __builtin_amdgcn_s_sleep(1);
     }
+    if (polls == most) *lost = 1;
 #pragma unroll
     for (int k = 0; k < kAtOnce; ++k) {
       const uint32_t w = first + k * kK1Block;
@@ -139,7 +145,7 @@ __device__ void control(const UpdateArgs& u, const SelectArgs& s, const uint64_t
   const int b = int(threadIdx.x), l = b & 63;
   const int wave = __builtin_amdgcn_readfirstlane(b >> 6);
   const bool has = b < u.num_units;
-  const uint32_t tag = *launches + 1;
+  const uint32_t tag = tag_of(*launches);
   const uint32_t late_from = num > kLate ? num - kLate : 0;
   UnitPast past{};
   int32_t lo = 0, hi = 0;
@@ -170,9 +176,10 @@ __device__ void control(const UpdateArgs& u, const SelectArgs& s, const uint64_t
     }
     if (has) sh.unit[late ? at : n_late + (b - at)] = b;
   }
+  if (l == 0) sh.lost[wave] = 0;
 #pragma unroll 1
   for (uint32_t from = 0, to = late_from > 0 ? late_from : num;;) {
-    collect(words, num, from, to, tag, part);
+    collect(words, num, from, to, tag, part, &sh.lost[wave]);
     __syncthreads();
     const bool end = to == num;
     if (lanes != 1) {
@@ -230,7 +237,8 @@ __device__ void control(const UpdateArgs& u, const SelectArgs& s, const uint64_t
   }
   if (b == 0) {
     finish_step(s, past.t, tot);
-    *launches = tag;  // (every item has read it: its word has arrived)
+    // (every item has read it if its word has arrived)
+    *launches = launches_after(tag, (sh.lost[0] | sh.lost[1] | sh.lost[2] | sh.lost[3]) == 0);
   }
 }
 
@@ -248,10 +256,10 @@ __global__ __launch_bounds__(kK1Block, 5) void k123_step(const Item* __restrict_
     control(u, s, words, launches, num_items, lanes, part, sh);
     return;
   }
-  const uint32_t w = blockIdx.x - 1, tag = *launches + 1;
+  const uint32_t w = blockIdx.x - 1, tag = tag_of(*launches);
   const Item it = items[xcd_item(w, num_items)];
   const float ss = item_sumsq(it, seg_base.of(it.seg), seg_dtype[it.seg], part);
-  if (threadIdx.x == 0)
+  if (threadIdx.x == 0 && !words_lost(tag))
     __hip_atomic_store(words + w, uint64_t(tag) << 32 | __float_as_uint(ss), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
