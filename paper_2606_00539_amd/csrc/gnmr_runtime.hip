@@ -264,7 +264,8 @@ gnmr_status check_ptrs(const gnmr_ctx* c, const void* const* ptrs) {
 
 // Checks this step's segment pointers and copies them to the device table on
 // `st`; or, when they are few enough to go with the K1 launch and `passed` is
-// given, leaves them in *passed for it.
+// given, leaves them in *passed for it (the launch fills the table: they are bound
+// once it is made).
 gnmr_status bind_ptrs(gnmr_ctx* c, const void* const* ptrs, hipStream_t st,
                       const void* const** passed = nullptr) {
   if (ptrs == nullptr) {
@@ -277,7 +278,6 @@ gnmr_status bind_ptrs(gnmr_ctx* c, const void* const* ptrs, hipStream_t st,
   if (c->S == 0) return GNMR_OK;
   if (passed != nullptr && c->num_items > 0 && c->S <= gnmr::kK1MostPassed) {
     *passed = ptrs;
-    c->ptrs_bound = true;
     return GNMR_OK;
   }
   if (c->upload_pending) {
@@ -599,12 +599,14 @@ gnmr_status gnmr_step(gnmr_ctx* ctx, double alpha_t, double beta_t, const void* 
     control_args(ctx, nullptr, nullptr, ctx->d_unit_item_off, alpha_t, beta_t, u, s);
     GNMR_HIP(gnmr::launch_step(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
                                ctx->d_seg_dtype, ctx->d_words, ctx->d_launches, u, s, st));
+    if (passed != nullptr) ctx->ptrs_bound = true;
     return GNMR_OK;
   }
   r = record(ctx, 0, st);
   if (r != GNMR_OK) return r;
   GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
                               ctx->d_seg_dtype, ctx->d_partial, st));
+  if (passed != nullptr) ctx->ptrs_bound = true;
   r = record(ctx, 1, st);
   if (r != GNMR_OK) return r;
   return update_and_select(ctx, nullptr, ctx->d_partial, ctx->d_unit_item_off, ctx->num_items,
@@ -768,6 +770,7 @@ gnmr_status gnmr_sumsq(gnmr_ctx* ctx, const void* const* seg_ptr, double* d_sums
   if (r != GNMR_OK) return r;
   GNMR_HIP(gnmr::launch_sumsq(ctx->d_items, ctx->num_items, ctx->d_seg_base, passed, ctx->S,
                               ctx->d_seg_dtype, ctx->d_partial, st));
+  if (passed != nullptr) ctx->ptrs_bound = true;
   GNMR_HIP(gnmr::launch_unit_sumsq(ctx->d_unit_item_off, ctx->d_partial, ctx->num_items,
                                    ctx->U, d_sumsq, st));
   return GNMR_OK;
