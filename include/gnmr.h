@@ -293,9 +293,8 @@ gnmr_status gnmr_profile_read(gnmr_ctx* ctx, double* ms_sumsq, double* ms_update
                               double* ms_select, int64_t* steps);
 
 /* Work-list facts: K1 work items, bytes per item, gradient bytes per step and
- * the kernels that a gnmr_step is made of, each a launch while profiling (up to
- * 256 units of up to 6,144 items in all: one launch for all of them otherwise).
- * Any output may be NULL. */
+ * the kernel launches of a gnmr_step (up to 256 units of up to 6,144 items in
+ * all: 1, or while profiling 2 or 3).  Any output may be NULL. */
 gnmr_status gnmr_info(const gnmr_ctx* ctx, int64_t* num_items, int64_t* item_bytes,
                       int64_t* bytes_per_step, int32_t* launches_per_step);
 

@@ -1035,8 +1035,11 @@ gnmr_status gnmr_info(const gnmr_ctx* ctx, int64_t* num_items, int64_t* item_byt
   if (launches_per_step) {
     gnmr::UpdateArgs u{};
     u.num_units = ctx->U;
-    *launches_per_step = (ctx->num_items > 0 ? 1 : 0) +
-                         (gnmr::single_launch_update_select(u, ctx->num_items) ? 1 : 2);
+    const bool one = ctx->d_words != nullptr && !ctx->prof;  // as in gnmr_step
+    *launches_per_step =
+        one ? 1
+            : (ctx->num_items > 0 ? 1 : 0) +
+                  (gnmr::single_launch_update_select(u, ctx->num_items) ? 1 : 2);
   }
   return GNMR_OK;
 }

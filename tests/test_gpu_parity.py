@@ -44,8 +44,8 @@ def test_tiny_end_to_end(gen):
     lay = L.for_workload(w)
     buf, base, ptrs = device_buffer(torch, lay)
     with controller_for(lay, w, ptrs) as ctl:
-        # K1, then K2 + K3 in one workgroup (28 units of a few items each)
-        assert ctl.info()["launches_per_step"] == 2
+        # all three kernels in one launch (28 units of a few items each)
+        assert ctl.info()["launches_per_step"] == 1
         for t in range(1, w.steps + 1):
             gen.fill(lay, base, w.seed, t, w.scale32(t, nudge[t - 1]))
             ctl.step(alphas[t - 1], betas[t - 1])
@@ -116,11 +116,12 @@ def test_sumsq_ragged_layouts(gen, misaligned):
 
 @pytest.mark.parametrize("case", ["ragged_misaligned", "bf16_128_units", "bf16_1024_units"])
 def test_small_step_matches_norm_path(gen, case):
-    """A small workload's step (K1, then K2 and K3 in one workgroup) against
-    the same steps taken as K1 and the unit sums, then the controller from
-    those norms: every output bit-identical, step after step; the norms also
-    within the bar of the oracle's sum of squares.  bf16_1024_units sits at
-    the single workgroup's limit: 1,024 units of one work item each."""
+    """A small workload's step (one launch, or K1, then K2 and K3 in one
+    workgroup) against the same steps taken as K1 and the unit sums, then the
+    controller from those norms: every output bit-identical, step after step;
+    the norms also within the bar of the oracle's sum of squares.
+    bf16_1024_units sits at the single workgroup's limit: 1,024 units of one
+    work item each."""
     torch = require_gpu()
     rng = np.random.default_rng(11)
     if case == "ragged_misaligned":
@@ -135,7 +136,7 @@ def test_small_step_matches_norm_path(gen, case):
         dtypes = [V.DTYPE_BF16] * 1024
         pieces = [[n] for n in sizes]
         lay = L.build(sizes, dtypes)
-    launches = 2
+    launches = 2 if case == "bf16_1024_units" else 1
     U = len(sizes)
     say("small step vs norm path:", case, "units", U, "segments", lay.num_segments)
     buf, base, ptrs = device_buffer(torch, lay)

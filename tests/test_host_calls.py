@@ -68,10 +68,24 @@ static int unbound(int units, int segs, long numel, int sumsq, int prof) {
   return gnmr_destroy(c);
 }
 
+static int launches(int units, int segs, long numel, int prof) {
+  gnmr_ctx* c = context(units, segs, numel);
+  const void** p = pointers((int64_t)units * segs);
+  int32_t said = -1;
+  NEED(gnmr_set_profiling(c, prof));
+  NEED(gnmr_info(c, NULL, NULL, NULL, &said));
+  fake_launches = 0;
+  NEED(gnmr_step(c, 1.1, 1.3, p, NULL));
+  printf("%d %d\n", (int)said, fake_launches);
+  free(p);
+  return gnmr_destroy(c);
+}
+
 int main(int argc, char** argv) {
   long v[5] = {0};
   for (int k = 2; k < argc && k < 7; ++k) v[k - 2] = atol(argv[k]);
   if (!strcmp(argv[1], "unbound")) return unbound((int)v[0], (int)v[1], v[2], (int)v[3], (int)v[4]);
+  if (!strcmp(argv[1], "launches")) return launches((int)v[0], (int)v[1], v[2], (int)v[3]);
   return 3;
 }
 """
@@ -105,3 +119,14 @@ def test_a_failed_launch_binds_no_pointers(program, units, segs, sumsq, prof):
     """The launch itself leaves the pointers in the device table: after one that
     failed, a step without pointers is refused, and none reads the empty table."""
     program("unbound", units, segs, 5000, sumsq, prof)
+
+
+# Up to 256 units of up to 6,144 work items of 32,768 values: one launch, or, while
+# profiling, K1 and K2 + K3 as one or two.  A step without items has no K1.
+@pytest.mark.parametrize("units,numel,plain,profiling", [
+    (28, 65536, 1, 2), (256, 24 * 32768, 1, 2), (256, 24 * 32768 + 1, 2, 2), (1, 6144 * 32768, 1, 2),
+    (1, 6145 * 32768, 2, 2), (84, 73 * 32768, 1, 3), (257, 10, 2, 2), (1024, 10, 2, 2),
+    (1025, 10, 3, 3), (5, 0, 1, 1), (2000, 0, 2, 2)])
+def test_info_gives_the_launches_of_a_step(program, units, numel, plain, profiling):
+    for prof, want in ((0, plain), (1, profiling)):
+        assert program("launches", units, 1, numel, prof).split() == [str(want)] * 2
