@@ -16,8 +16,9 @@ HEADERS = [os.path.join(PKG, "csrc", f)
            for f in ("gnmr_internal.h", "k1_geometry.h", "k1_item.h", "k3_pool.h", "lane_ops.h",
                      "launch_tag.h", "unit_step.h")] + [os.path.join(ROOT, "include", "gnmr.h")]
 
-# Marshalling of the per-step calls for Python (host code).
-CALLS = os.path.join(PKG, "_calls.so")
+# Marshalling of the per-step calls (host code), for the Python that builds it: the
+# name carries that Python's ABI, so that no other one loads it.
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 CALLS_SOURCE = os.path.join(PKG, "csrc", "py_calls.c")
 
 # Packed-fp32 instructions are switched off for all device code.
@@ -48,6 +49,9 @@ def build_calls(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(CALLS + ".tmp", CALLS)
+    untagged = os.path.join(PKG, "_calls.so")   # any Python would load one left by an older build
+    if os.path.exists(untagged):
+        os.remove(untagged)
     return CALLS
 
 

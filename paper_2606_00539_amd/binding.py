@@ -9,7 +9,9 @@ fallback.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 import numpy as np
 
@@ -132,19 +134,73 @@ def load_library(path: str = _LIB_PATH) -> ctypes.CDLL:
 
 # The entry points of a training step are called through csrc/py_calls.c: ctypes and
 # Python marshalled for longer than the small calls' kernels run.  All others stay
-# with ctypes.
+# with ctypes, and so do these under a Python that the module is not built for.
 _PER_STEP = ("gnmr_step", "gnmr_step_from_norms", "gnmr_step_from_partials", "gnmr_sumsq",
              "gnmr_actuate", "gnmr_actuate_matrix", "gnmr_wgrad_sumsq",
              "gnmr_wgrad_sumsq_batched")
 
 
+class _CtypesCalls:
+    """The functions of the module _calls by ctypes."""
+
+    def __init__(self, lib):
+        self.bind(lib, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value
+                        for n in _PER_STEP})
+
+    def bind(self, lib, addresses):
+        """Calls what is at `addresses`, with the argument types of lib's functions."""
+        self._f = {n: ctypes.CFUNCTYPE(ctypes.c_int, *getattr(lib, n).argtypes)(a)
+                   for n, a in addresses.items()}
+
+    def step(self, ctx, alpha_t, beta_t, seg_ptr, stream):
+        ptrs = None if seg_ptr is None else _ptr_array(seg_ptr)
+        return self._f["gnmr_step"](ctx, float(alpha_t), float(beta_t), ptrs, _stream(stream))
+
+    def sumsq(self, ctx, seg_ptr, d_sumsq, stream):
+        ptrs = None if seg_ptr is None else _ptr_array(seg_ptr)
+        return self._f["gnmr_sumsq"](ctx, ptrs, _dptr(d_sumsq), _stream(stream))
+
+    def step_from_norms(self, ctx, d_norm, alpha_t, beta_t, stream):
+        return self._f["gnmr_step_from_norms"](ctx, _dptr(d_norm), float(alpha_t), float(beta_t),
+                                               _stream(stream))
+
+    def step_from_partials(self, ctx, d_partial, alpha_t, beta_t, stream):
+        return self._f["gnmr_step_from_partials"](ctx, _dptr(d_partial), float(alpha_t),
+                                                  float(beta_t), _stream(stream))
+
+    def actuate(self, act, d_mask, fmt_low, fmt_recovery, stream):
+        return self._f["gnmr_actuate"](act, _dptr(d_mask), int(fmt_low), int(fmt_recovery),
+                                       _stream(stream))
+
+    def actuate_matrix(self, x, out, rows, cols, d_mask, unit, fmt_low, fmt_recovery, stream):
+        return self._f["gnmr_actuate_matrix"](_dptr(x), _dptr(out), int(rows), int(cols),
+                                              _dptr(d_mask), int(unit), int(fmt_low),
+                                              int(fmt_recovery), _stream(stream))
+
+    def wgrad_sumsq(self, dy, x, dw, tokens, out_features, in_features, tile_sumsq, stream):
+        return self._f["gnmr_wgrad_sumsq"](_dptr(dy), _dptr(x), _dptr(dw), int(tokens),
+                                           int(out_features), int(in_features),
+                                           _dptr(tile_sumsq), _stream(stream))
+
+    def wgrad_sumsq_batched(self, problems, tile_sumsq, stream):
+        ps = []
+        for p in problems:
+            a, b, c, t, o, i = p[:6]
+            ps.append(gnmr_wgrad_problem(_dptr(a), _dptr(b), _dptr(c), int(t), int(o), int(i),
+                                         int(p[6]) if len(p) > 6 else 0, 0))
+        arr = (gnmr_wgrad_problem * max(len(ps), 1))(*ps)
+        return self._f["gnmr_wgrad_sumsq_batched"](arr, len(ps), _dptr(tile_sumsq),
+                                                   _stream(stream))
+
+
 def _load_calls(lib):
     """The module of the per-step calls, set to the functions of `lib`."""
     try:
-        from . import _calls as calls
-    except ImportError as e:
-        raise RuntimeError(f"the module _calls is not built; run __graft_entry__.build() first "
-                           f"({e})") from e
+        calls = importlib.import_module("._calls", __package__)
+    except ModuleNotFoundError:
+        warnings.warn("the module _calls is not built for this Python (__graft_entry__.build() "
+                      "does it): the per-step calls take longer through ctypes", RuntimeWarning)
+        return _CtypesCalls(lib)
     calls.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _PER_STEP})
     return calls
 

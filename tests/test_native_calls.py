@@ -1,6 +1,12 @@
 """The compiled marshalling of the per-step calls hands the C entry points what
-ctypes and plain Python conversions hand them, for every form of an argument."""
+ctypes and plain Python conversions hand them, for every form of an argument; and so
+does what takes its place under a Python that it is not built for."""
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
+import sysconfig
 from collections import namedtuple
 
 import numpy as np
@@ -50,11 +56,10 @@ class Rows:
 Problem = namedtuple("Problem", "dy x dw tokens outf inf acc")
 
 
-@pytest.fixture
-def seen():
+def recording():
     """Binds the module to functions that record what they are given; -7 is
     the status they return."""
-    calls, keep, got = B._native(), [], []
+    keep, got = [], []
 
     def record(name):
         def f(*a):
@@ -80,11 +85,29 @@ def seen():
     for name, args in SIGNATURES.items():
         fns[name] = ctypes.CFUNCTYPE(ctypes.c_int, *args)(record(name))
     keep.append(fns)
-    calls.bind({n: ctypes.cast(f, P).value for n, f in fns.items()})
+    return keep, got, {n: ctypes.cast(f, P).value for n, f in fns.items()}
+
+
+@pytest.fixture
+def seen():
+    calls = B._native()
+    keep, got, addresses = recording()
+    calls.bind(addresses)
     try:
         yield calls, got
     finally:
         calls.bind({n: ctypes.cast(getattr(B.load_library(), n), P).value for n in B._PER_STEP})
+
+
+@pytest.fixture(params=["compiled", "ctypes"])
+def either(request):
+    if request.param == "compiled":
+        yield request.getfixturevalue("seen")
+    else:
+        keep, got, addresses = recording()
+        calls = B._CtypesCalls(B.load_library())
+        calls.bind(B.load_library(), addresses)
+        yield calls, got
 
 
 def pointer(p):
@@ -121,8 +144,8 @@ def same(a, b):
 
 
 @pytest.mark.parametrize("k", range(10))
-def test_every_form_of_an_argument(seen, k):
-    calls, got = seen
+def test_every_form_of_an_argument(either, k):
+    calls, got = either
     p, q, r = (POINTERS[(k + j) % len(POINTERS)] for j in (0, 3, 5))
     s, h = STREAMS[k % len(STREAMS)], HANDLES[k % len(HANDLES)]
     w, v = WHOLE[k % len(WHOLE)], WHOLE[(k + 1) % len(WHOLE)]
@@ -143,8 +166,8 @@ def test_every_form_of_an_argument(seen, k):
 # around the 256 pointers that are marshalled on the stack
 @pytest.mark.parametrize("n", [0, 1, 10, 255, 256, 257, 5000])
 @pytest.mark.parametrize("form", [list, tuple, iter, np.array])
-def test_pointer_lists(seen, n, form):
-    calls, got = seen
+def test_pointer_lists(either, n, form):
+    calls, got = either
     got.count = max(n, 1)
     vals = [POINTERS[i % len(POINTERS)] for i in range(n)]
     if form is np.array:
@@ -156,8 +179,8 @@ def test_pointer_lists(seen, n, form):
     assert calls.step(5, 1.0, 2.0, None, 9) == -7 and got[2] == ([5, 1.0, 2.0, False, 9], [])
 
 
-def test_problems(seen):
-    calls, got = seen
+def test_problems(either):
+    calls, got = either
     ps = [(X, 4096, Buffer(64), 10, 20, 30), [X, X, X, 1.9, 2**32 + 8, 16, True],
           Problem(16, 32, 48, 2**40, 8, 8, 1), Rows(16, 32, 48, 5, 6, 7),
           Rows(16, 32, 48, 5, 6, 7, 1), (16, 32, 48, 1, 2, 3, 1, "more")] * 9
@@ -204,3 +227,37 @@ def test_other_refusals(seen, call):
     with pytest.raises((TypeError, ValueError, AttributeError)):
         call(calls)
     assert not got
+
+
+def test_the_module_is_the_compiled_one():
+    assert B._native().__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_another_python_does_not_load_the_module(tmp_path):
+    """The package in a copy whose module is that of another Python: it loads, says
+    so, and calls through ctypes."""
+    pkg = os.path.dirname(B.__file__)
+    ext = sysconfig.get_config_var("EXT_SUFFIX")
+    copy = shutil.copytree(pkg, tmp_path / "paper_2606_00539_amd",
+                           ignore=shutil.ignore_patterns("__pycache__", "csrc"))
+    os.rename(copy / ("_calls" + ext), copy / "_calls.cpython-399-x86_64-linux-gnu.so")
+    code = """
+import warnings
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    import paper_2606_00539_amd as g
+    from paper_2606_00539_amd import binding as B
+    assert type(B._native()).__name__ == "_CtypesCalls"
+    assert any("not built for this Python" in str(w.message) for w in seen)
+for call in (lambda: g.gnmr_step(None, 1.0, 1.0), lambda: g.gnmr_actuate(None, 4096, 1, 0),
+             lambda: g.gnmr_wgrad_sumsq(4096, 8192, 16384, 16, 12, 128, 32768)):
+    try:
+        call()
+        raise SystemExit("accepted")
+    except g.GnmrError as e:
+        assert e.status == g.binding.GNMR_E_INVALID, e
+print("good")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True,
+                       env={k: v for k, v in os.environ.items() if k != "GNMR_LIBRARY"}, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == "good", r.stdout + r.stderr
