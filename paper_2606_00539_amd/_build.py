@@ -42,9 +42,13 @@ def build(verbose: bool = True) -> str:
     return LIB
 
 
+def calls_command(out_path: str, *flags: str) -> list:
+    return ["gcc", "-O2", "-fPIC", "-shared", "-Wall", *flags, "-I", os.path.join(ROOT, "include"),
+            "-I", sysconfig.get_paths()["include"], "-o", out_path, CALLS_SOURCE]
+
+
 def build_calls(verbose: bool = True) -> str:
-    cmd = ["gcc", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
-           "-I", sysconfig.get_paths()["include"], "-o", CALLS + ".tmp", CALLS_SOURCE]
+    cmd = calls_command(CALLS + ".tmp")
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
