@@ -441,17 +441,46 @@ __global__ __launch_bounds__(kK3Block) void k3_select(SelectArgs a) {
         }
         __builtin_amdgcn_s_waitcnt(0);
       } else {
-        // smaller workgroups, or more of them than threads: one to 64 threads each
+        // Smaller workgroups, or more of them than threads: one to 64 threads each,
+        // two latencies a round; or, where that is more than twice as many rounds,
+        // candidate i to thread i: bisection finds the thread that counted it, that
+        // thread's counts the workgroup.  Us a step with threads to the workgroups and
+        // to the candidates: 300,000 units, 1,000 and 16,000 candidates 52.7 and 15.5,
+        // 74.4 and 43.5; 2,000,000, 4,000 candidates 262 and 61.8; workgroups of four,
+        // 10,000 units, 1,251 and 10,000 candidates 22.1 and 17.7, 24.6 and 32.9.
         const int group = a.wg_shift < 6 ? 1 << a.wg_shift : 64;
-        for (int t = tid / group; t * per < a.num_wgs; t += kK3Block / group) {
-          int off = s_off[t];
-          for (int w = t * per; w < (t + 1) * per && w < a.num_wgs; ++w) {
-            const int cnt = count_of(a.wg_counts[w], kCntCand);
-            for (int j = tid & (group - 1); j < cnt; j += group) {
-              s_rank[off + j] = a.pool_rank[(int64_t(w) << a.wg_shift) + j];
-              s_unit[off + j] = a.pool_unit[(int64_t(w) << a.wg_shift) + j];
+        if (pool_rounds(uint32_t(a.num_wgs) * uint32_t(group), kK3Block) <=
+            2u * pool_rounds(uint32_t(n_cand), kK3Block)) {
+          for (int t = tid / group; t * per < a.num_wgs; t += kK3Block / group) {
+            int off = s_off[t];
+            for (int w = t * per; w < (t + 1) * per && w < a.num_wgs; ++w) {
+              const int cnt = count_of(a.wg_counts[w], kCntCand);
+              for (int j = tid & (group - 1); j < cnt; j += group) {
+                s_rank[off + j] = a.pool_rank[(int64_t(w) << a.wg_shift) + j];
+                s_unit[off + j] = a.pool_unit[(int64_t(w) << a.wg_shift) + j];
+              }
+              off += cnt;
             }
-            off += cnt;
+          }
+        } else {
+          for (int i = tid; i < n_cand; i += kK3Block) {
+            int t = 0;
+#pragma unroll 1
+            for (int half = kK3Block / 2; half > 0; half /= 2)
+              t += s_off[t + half] <= i ? half : 0;
+            const int first = i - s_off[t];
+            int w = t * per, j = first, seen = 0;
+#pragma unroll 4
+            for (int k = 1; k < per; ++k) {
+              // (past the last workgroup all of them are seen: nothing moves any more)
+              seen += count_of(a.wg_counts[min(t * per + k, a.num_wgs) - 1], kCntCand);
+              if (seen <= first) {
+                w = t * per + k;
+                j = first - seen;
+              }
+            }
+            s_rank[i] = a.pool_rank[(int64_t(w) << a.wg_shift) + j];
+            s_unit[i] = a.pool_unit[(int64_t(w) << a.wg_shift) + j];
           }
         }
       }

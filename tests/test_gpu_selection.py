@@ -124,3 +124,18 @@ def test_one_and_two_launch_steps(U, parts):
             ref = ora.step(np.sqrt(np.array(sums)), 1.1, 1.5)
             # float64 sums of up to 10,241 positive terms in two orders: 2 n 2^-53
             assert_step_matches(ctl.query(), ref, rtol=1e-11, what=f"t={t}")
+
+
+# Sparse pools over more K2 workgroups of 256 units than the selection has threads
+# (two, four and five to a thread, the last one ragged): scattered candidates and
+# neighbouring ones, up to one and several rounds of threads.
+@pytest.mark.parametrize("U,pool,together", [
+    (262145, 300, False), (262145, 1025, True), (300000, 1000, False), (524289, 2500, True),
+    (700001, 9000, False), (1048577, 1, False), (1048577, 16384, True)])
+def test_sparse_pool_of_many_units(U, pool, together):
+    print(f"sparse pool U={U} pool={pool} together={together}", flush=True)
+    rng = np.random.default_rng(U + pool)
+    base = np.exp(rng.normal(scale=0.01, size=(3, U)))
+    hot = np.arange(U - pool, U) if together else rng.permutation(U)[:pool]
+    base[1:, hot] *= 3.0 + rng.random((2, pool))
+    run(U, base, max_o=max(0, pool // 3), alpha=1.2)
