@@ -139,3 +139,22 @@ def test_sparse_pool_of_many_units(U, pool, together):
     hot = np.arange(U - pool, U) if together else rng.permutation(U)[:pool]
     base[1:, hot] *= 3.0 + rng.random((2, pool))
     run(U, base, max_o=max(0, pool // 3), alpha=1.2)
+
+
+# Every candidate tied, exactly or within the keys' lower halves, and half of them
+# non-finite: in registers, in LDS and in memory, cut within the tie.
+@pytest.mark.parametrize("U", [130, 1000, 3000, 16385, 42496])
+@pytest.mark.parametrize("kind", ["equal", "near", "infinite", "half"])
+def test_ties_over_the_whole_pool(U, kind):
+    print(f"whole pool tied U={U} {kind}", flush=True)
+    rng = np.random.default_rng(U)
+    base = np.ones((4, U))
+    if kind == "near":
+        base[2:] *= 1.0 + 1e-14 * rng.integers(0, 5, (2, U))
+    elif kind == "infinite":
+        base[2:] = np.inf
+    elif kind == "half":
+        base *= np.exp(rng.normal(scale=0.05, size=(4, U)))
+        base[2:, rng.permutation(U)[:U // 2]] = np.inf
+    for max_o in (1, U // 3, U - 1):
+        run(U, base, max_o=max_o, alpha=0.4)
