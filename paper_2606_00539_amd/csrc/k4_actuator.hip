@@ -106,8 +106,9 @@ __device__ __forceinline__ u32x4 load(const g_cvec* p) {
 }
 
 // Row `row` of segment sg (none when !valid) by LANES lanes of kVpt vectors
-// each; kUniform: a wavefront's rows are of one unit.  Every lane of the workgroup calls it, and a row of more than 64 lanes
-// has the workgroup to itself; `red` is then LDS of LANES / 64 floats.
+// each; kUniform: a wavefront's rows are of one unit.  Every lane of the workgroup
+// calls it, and a row of more than 64 lanes has the workgroup to itself; `red` is
+// then LDS of LANES / 64 floats.
 template <int LANES, int kVpt, bool kCached, bool kUniform>
 __device__ __forceinline__ void actuate_row(const ActSeg sg, int64_t row, bool valid,
                                             const uint8_t* __restrict__ mask, int fmt_low,
@@ -220,7 +221,7 @@ GNMR_K4_KERNEL void k4_actuate(const RowItem* __restrict__ items, uint32_t num_r
   const ActSeg sg = segs[it.seg];
   __builtin_amdgcn_sched_barrier(0);  // the whole entry at once, not the pointers after the mask
   actuate_row<LANES, kVpt, kCached, LANES >= 64>(sg, it.row, valid, mask, fmt_low, fmt_rec,
-                                    int(threadIdx.x) % LANES, red);
+                                                 int(threadIdx.x) % LANES, red);
 }
 
 // One matrix without a row table (the segment passed by value).
@@ -232,7 +233,7 @@ GNMR_K4_KERNEL void k4_matrix(const ActSeg sg, uint32_t num_rows,
   const uint32_t sub = kRows > 1 ? threadIdx.x / LANES : 0;
   const uint32_t r = xcd_order(blockIdx.x, gridDim.x) * kRows + sub;
   actuate_row<LANES, kVpt, kCached, true>(sg, r, r < num_rows, mask, fmt_low, fmt_rec,
-                                    int(threadIdx.x) % LANES, red);
+                                          int(threadIdx.x) % LANES, red);
 }
 
 // Calls f.template operator()<LANES, kVpt>() for a row class.  The lanes and
@@ -260,24 +261,25 @@ void for_class(int cls, const F& f) {
   else if constexpr (kClass + 1 < kK4Classes) for_class<kClass + 1>(cls, f);
 }
 
-// The classes whose workgroups have kK4Block lanes.
-constexpr int kMixed = 10;
-static_assert(block_of(kClasses[kMixed - 1].lanes) == kK4Block &&
-              block_of(kClasses[kMixed].lanes) > kK4Block, "");
-
-// Rows of several classes in one launch: workgroups [block[c], block[c + 1]) take
-// rows [row[c], row[c + 1]) of the table.
+// Rows of several classes in one launch of workgroups of kK4Block lanes:
+// workgroups [block[c], block[c + 1]) take rows [row[c], row[c + 1]) of the table.
 struct MixedRows {
-  uint32_t block[kMixed + 1], row[kMixed + 1];
+  uint32_t block[kK4Classes + 1], row[kK4Classes + 1];
 };
 
-template <int kClass = 0>
+constexpr RowClass mixed_class(int c) {
+  return kClasses[c].lanes <= kK4Block
+             ? kClasses[c]
+             : RowClass{kK4Block, kClasses[c].vpt * (kClasses[c].lanes / kK4Block)};
+}
+
+template <bool kCached, int kClass = 0>
 __device__ __forceinline__ void mixed_row(int cls, uint32_t w, const MixedRows& rows,
                                           const RowItem* items, const ActSeg* segs,
                                           const uint8_t* mask, int fmt_low, int fmt_rec,
                                           float* red) {
   if (cls == kClass) {
-    constexpr int kLanes = kClasses[kClass].lanes;
+    constexpr int kLanes = mixed_class(kClass).lanes;
     const uint32_t sub = kLanes < kK4Block ? threadIdx.x / kLanes : 0;
     // (each class over all XCDs: its workgroups have less or more to do than others)
     const uint32_t at =
@@ -287,13 +289,14 @@ __device__ __forceinline__ void mixed_row(int cls, uint32_t w, const MixedRows& 
     const RowItem it = items[valid ? r : rows.row[kClass + 1] - 1];
     const ActSeg sg = segs[it.seg];
     __builtin_amdgcn_sched_barrier(0);
-    actuate_row<kLanes, kClasses[kClass].vpt, true, kLanes >= 64>(
+    actuate_row<kLanes, mixed_class(kClass).vpt, kCached, kLanes >= 64>(
         sg, it.row, valid, mask, fmt_low, fmt_rec, int(threadIdx.x) % kLanes, red);
-  } else if constexpr (kClass + 1 < kMixed) {
-    mixed_row<kClass + 1>(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
+  } else if constexpr (kClass + 1 < kK4Classes) {
+    mixed_row<kCached, kClass + 1>(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
   }
 }
 
+template <bool kCached>
 __global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 6))) void k4_mixed(
     const RowItem* __restrict__ items, const MixedRows rows, const ActSeg* __restrict__ segs,
     const uint8_t* __restrict__ mask, int fmt_low, int fmt_rec) {
@@ -301,8 +304,8 @@ __global__ __launch_bounds__(kK4Block) __attribute__((amdgpu_waves_per_eu(6, 6))
   const uint32_t w = blockIdx.x;
   int cls = 0;
 #pragma unroll
-  for (int c = 1; c < kMixed; ++c) cls = w >= rows.block[c] ? c : cls;
-  mixed_row(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
+  for (int c = 1; c < kK4Classes; ++c) cls = w >= rows.block[c] ? c : cls;
+  mixed_row<kCached>(cls, w, rows, items, segs, mask, fmt_low, fmt_rec, red);
 }
 
 struct TableLaunch {
@@ -366,35 +369,66 @@ int k4_class(int cols) {
   return c;
 }
 
-// Tables small enough for cached loads take one launch for all classes present but
-// the two of 512 lanes, where a launch per class takes 1.5 to 4 us more: the inputs
-// of layers' projections, two widths, per class and in one launch, 8.1 and 4.1 us
-// (2.8 MB), 10.1 and 6.4 (8.1 MB), 14.0 and 11.7 (22.5 MB), 26.1 and 23.6 (61 MB).
-// (All rows by the widest class's kernel: 5.0, 7.6 and 18.4 of the first three.)
+namespace {
+
+// Whether all classes of a table take one launch, which the longest row's registers
+// then limit to six waves per SIMD, or a launch each, each with a start and a tail
+// of its own.  With cached loads one launch: the inputs of layers' projections, two
+// widths, a launch each and one, 7.4 and 4.7 us (5120 and 13824 features, 0.9 MB),
+// 8.3 and 5.6 (3.9 MB), 24.3 and 21.6 (63 MB), twelve widths 41 and 4.9 (0.9 MB),
+// 62 and 24.6 (63 MB).  (A workgroup of 256 lanes with eight vectors each for every
+// row: 5.0, 5.6 and 28.0 of the first three.)  Past that, rows of up to 1,024 features
+// want eight waves and lose about 0.05 us a MB, against 2 us for each further launch:
+// 28 inputs of 1024 and 2816, a launch each and one, 31.2 and 32.9 us (49 MB of the
+// narrow), 74 and 83 (170 MB); 256, 512 and 4096 62.6 and 60.7 (100 MB); 2048 and 5504
+// 38.7 and 36.2 (none, 100 MB in all); twelve widths 73.8 and 41.8 (33 MB), 186 and 149
+// (133 MB).  A large table's launches are long beside what they cost: 4096 and 11008 at
+// 500 MB 162 and 165, 1 GB 322 and 323.
+constexpr int64_t kMixedBytes = int64_t(384) << 20, kMixedNarrow = int64_t(32) << 20;
+bool one_launch(const int64_t* class_off, int64_t bytes) {
+  int present = 0;
+  int64_t narrow = 0;  // at most these bytes are of rows up to 1,024 features
+  for (int c = 0; c < kK4Classes; ++c) {
+    const int64_t rows = class_off[c + 1] - class_off[c];
+    const int widest = kClasses[c].lanes * kClasses[c].vpt * 8;
+    present += rows > 0 ? 1 : 0;
+    if (widest <= 1024) narrow += rows * widest * 2;
+  }
+  if (present < 2 || bytes > kMixedBytes) return false;
+  return bytes <= kK4CachedBytes || narrow <= kMixedNarrow * (present - 1);
+}
+
+template <bool kCached>
+void launch_mixed(const RowItem* items, const int64_t* class_off, const ActSeg* segs,
+                  const uint8_t* mask, int fmt_low, int fmt_rec, hipStream_t s) {
+  MixedRows m{};
+  uint32_t blocks = 0;
+  for (int c = 0; c <= kK4Classes; ++c) {
+    m.block[c] = blocks;
+    m.row[c] = uint32_t(class_off[c]);
+    if (c == kK4Classes) break;
+    const int64_t per = kK4Block / mixed_class(c).lanes;
+    blocks += uint32_t((class_off[c + 1] - class_off[c] + per - 1) / per);
+  }
+  hipLaunchKernelGGL(k4_mixed<kCached>, dim3(blocks), dim3(kK4Block), 0, s, items, m, segs, mask,
+                     fmt_low, fmt_rec);
+}
+
+}  // namespace
+
 hipError_t launch_actuate(const RowItem* items, const int64_t* class_off, int64_t bytes,
                           const ActSeg* segs, const uint8_t* mask, int fmt_low, int fmt_rec,
                           hipStream_t s) {
-  int first = 0, present = 0;
-  for (int c = 0; c < kMixed; ++c) present += class_off[c + 1] > class_off[c] ? 1 : 0;
-  if (present > 1 && bytes <= kK4CachedBytes) {
-    MixedRows m{};
-    uint32_t blocks = 0;
-    for (int c = 0; c < kMixed; ++c) {
-      const int64_t per = kK4Block / kClasses[c].lanes, n = class_off[c + 1] - class_off[c];
-      m.block[c] = blocks;
-      m.row[c] = uint32_t(class_off[c]);
-      blocks += uint32_t((n + per - 1) / per);
-    }
-    m.block[kMixed] = blocks;
-    m.row[kMixed] = uint32_t(class_off[kMixed]);
-    hipLaunchKernelGGL(k4_mixed, dim3(blocks), dim3(kK4Block), 0, s, items, m, segs, mask, fmt_low,
-                       fmt_rec);
-    first = kMixed;
+  const bool cached = bytes <= kK4CachedBytes;
+  if (one_launch(class_off, bytes)) {
+    if (cached) launch_mixed<true>(items, class_off, segs, mask, fmt_low, fmt_rec, s);
+    else launch_mixed<false>(items, class_off, segs, mask, fmt_low, fmt_rec, s);
+    return hipGetLastError();
   }
-  for (int c = first; c < kK4Classes; ++c)
+  for (int c = 0; c < kK4Classes; ++c)
     if (class_off[c + 1] > class_off[c])
       for_class(c, TableLaunch{items + class_off[c], class_off[c + 1] - class_off[c], segs, mask,
-                               fmt_low, fmt_rec, bytes <= kK4CachedBytes, s});
+                               fmt_low, fmt_rec, cached, s});
   return hipGetLastError();
 }
 

@@ -93,8 +93,9 @@ def test_large_matrix_equals_its_parts(rows, cols):
     assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
 
 
-# one launch for the classes of up to 256 lanes with up to 64 MB of input, a launch
-# per class beyond; rows that fill their class's workgroups and rows that do not
+# all classes in one launch, with ordinary loads up to 64 MB of input and
+# non-temporal ones past it; rows that fill their class's workgroups and rows that
+# do not
 @pytest.mark.parametrize("rows", [1, 8, 33])
 @pytest.mark.parametrize("widths", [(8, 136), (1024, 2312), (128, 3080, 16384), tuple(WIDTHS)])
 @pytest.mark.parametrize("past", [0, 1])
@@ -122,3 +123,34 @@ def test_classes_of_a_small_table_in_one_launch(rows, widths, past):
             got = o.cpu().numpy().view(np.uint16).reshape(w.shape)
             assert np.array_equal(got, w), f"cols {w.shape[1]}"
     assert not filler.any()
+
+
+# a launch per class: past 384 MB, and past 64 MB where more than 32 MB for each
+# class but one are rows of up to 1,024 features; below either, one launch
+@pytest.mark.parametrize("widths,filler,rows", [
+    (tuple(WIDTHS), 16384, 12500), (tuple(WIDTHS), 16384, 11500),
+    ((2312,), 1024, 34000), ((1000, 8192, 12296), 512, 100000), ((1000, 8192, 12296), 512, 70000)])
+def test_classes_of_a_large_table(widths, filler, rows):
+    torch = require_gpu()
+    from paper_2606_00539_amd import Actuator
+
+    print(f"actuator large table {len(widths)} widths, {rows} x {filler}", flush=True)
+    rng = np.random.default_rng(rows)
+    acts = [rows_of(rng, r, c) for c in widths for r in (3, 33)]
+    U = len(acts) + 1
+    mask = (np.arange(U) % 2).astype(np.uint8)
+    mask[-1] = 0
+    fill = torch.zeros((rows, filler), dtype=torch.int16, device="cuda")
+    fill[rows - 1] = to_device(torch, rows_of(rng, 1, filler))[0]
+    last = fill[rows - 1].cpu().numpy().view(np.uint16)[None]
+    d_in = [to_device(torch, a) for a in acts]
+    d_out = [torch.full_like(t, 0x5555) for t in d_in]
+    segs = [(i, o, a.shape[0], a.shape[1], b)
+            for b, (i, o, a) in enumerate(zip(d_in, d_out, acts))]
+    with Actuator(segs + [(fill, fill, rows, filler, U - 1)], U) as act:
+        act.apply(torch.from_numpy(mask).to("cuda"), LOW, 3)
+        torch.cuda.synchronize()
+    for o, w in zip(d_out, FQ.actuate(acts, mask[:-1], LOW, 3)):
+        assert np.array_equal(o.cpu().numpy().view(np.uint16).reshape(w.shape), w), w.shape
+    got = fill[rows - 1].cpu().numpy().view(np.uint16)[None]
+    assert np.array_equal(got, FQ.fakequant_rows(last, LOW)) and not fill[:-1].any()
