@@ -106,12 +106,14 @@ struct WgProblem {
   int32_t accumulate;  // 1: add the product to the stored dw
 };
 
-struct WgBatch {
+template <int kMost>
+struct WgBatchOf {
   int32_t num;
   int32_t total_tiles;
-  int32_t tile_begin[kWgMaxBatch];  // each problem's first tile in the launch's tile order
-  WgProblem p[kWgMaxBatch];
+  int32_t tile_begin[kMost];  // each problem's first tile in the launch's tile order
+  WgProblem p[kMost];
 };
+typedef WgBatchOf<kWgMaxBatch> WgBatch;
 
 int64_t wgrad_tiles(int32_t M, int32_t N);
 hipError_t launch_wgrad(const WgBatch& batch, hipStream_t s);

@@ -70,11 +70,12 @@ struct Tile {
   static constexpr int kW = kT / 2;          // rows and columns of a wave's quarter
   static constexpr int kVec = kT / 8;        // 16-byte vectors per tile row
   static constexpr int kRow = kT + 32;       // LDS row stride: rows fall 64 B apart in the banks
-  static constexpr int kStage = kWgBK * kRow;                 // elements per operand and stage
-  static constexpr int kChunks = kWgBK * kVec / kWgThreads;   // 16-byte chunks per lane, operand and stage
-  static constexpr int kPass = kWgThreads / kVec;             // tile rows the workgroup covers at once
+  static constexpr int kStage = kWgBK * kRow;  // elements per operand and stage
+  // 16-byte chunks per lane, operand and stage; tile rows the workgroup covers at once
+  static constexpr int kChunks = kWgBK * kVec / kWgThreads;
+  static constexpr int kPass = kWgThreads / kVec;
   static constexpr int kAhead = kT == 256 ? 1 : kT == 128 ? 2 : 4;  // K steps in staging registers
-  static constexpr int kSets = kT == 64 ? 4 : 2;                   // fragment register sets
+  static constexpr int kSets = kT == 64 ? 4 : 2;                    // fragment register sets
 };
 // sched_group_barrier instruction classes
 constexpr int kSchedMfma = 0x008;
@@ -100,10 +101,14 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p0, const uint16_t* p1) {
 }
 
 // The problem that tile v of the launch belongs to; v becomes its tile there.
-__device__ __forceinline__ int problem_of(const WgBatch& batch, int& v) {
+// (A single problem has kernels of its own: 2 KiB of arguments and this search are
+// 0.5 us of the 6 to 10 that a small gradient takes.  8 x 48 of 5 tokens 6.2 and 5.7
+// us, 512 x 512 of 100 9.6 and 9.0, 4096 x 4096 of 64 12.9 and 12.2.)
+template <int kMost>
+__device__ __forceinline__ int problem_of(const WgBatchOf<kMost>& batch, int& v) {
   int pi = 0, begin = 0;
 #pragma unroll
-  for (int i = 1; i < kWgMaxBatch; ++i) {
+  for (int i = 1; i < kMost; ++i) {
     const int b = batch.tile_begin[i];  // INT32_MAX past the last problem
     if (v >= b) {
       pi = i;
@@ -168,8 +173,10 @@ __device__ __forceinline__ void wave_sum_to(float ss, float* red, int tid) {
 // kT: the tile edge.  256 writes the tile sums itself; the smaller tiles leave
 // them to k5_tile_sums.
 // kRows: accumulated tiles leave in full rows (rows_pay).
-template <bool kAcc, int kT, bool kRows = false>
-__global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(const WgBatch batch) {
+// kMost: the problems that a batch has room for.
+template <bool kAcc, int kT, bool kRows, int kMost>
+__global__ __launch_bounds__(kWgThreads, kT == 256 ? 1 : 2) void k5_wgrad(
+    const WgBatchOf<kMost> batch) {
   using G = Tile<kT>;
   constexpr int kB = G::kB, kW = G::kW, kRow = G::kRow, kChunks = G::kChunks, kPass = G::kPass;
   constexpr int kAhead = G::kAhead, kSets = G::kSets;
@@ -531,7 +538,8 @@ constexpr int kSumsThreads = 1024;
 // Sixteen waves, each with the part of one 256-tile wave that its row of
 // blocks i makes, add the squares in that kernel's order, so a tile sum has
 // the same bits on either path.
-__global__ __launch_bounds__(kSumsThreads) void k5_tile_sums(const WgBatch batch) {
+template <int kMost>
+__global__ __launch_bounds__(kSumsThreads) void k5_tile_sums(const WgBatchOf<kMost> batch) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[256 * 256];
   __shared__ float part[4][256];  // [block row i][lane of the 256-tile kernel]
   __shared__ float red[kWgThreads / 64];
@@ -597,18 +605,33 @@ bool rows_pay(const WgBatch& b) {
   return 2 * strided > b.total_tiles;
 }
 
+template <int kT, bool kAcc, bool kRows, int kMost>
+void launch_tiles(const WgBatchOf<kMost>& b, hipStream_t s) {
+  hipLaunchKernelGGL((k5_wgrad<kAcc, kT, kRows, kMost>), dim3(unsigned(b.total_tiles)),
+                     dim3(kWgThreads), 0, s, b);
+}
+
+template <int kT, int kMost>
+void launch_tiled(const WgBatchOf<kMost>& b, bool acc, bool rows, hipStream_t s) {
+  if (acc && rows) launch_tiles<kT, true, true>(b, s);
+  else if (acc) launch_tiles<kT, true, false>(b, s);
+  else launch_tiles<kT, false, false>(b, s);
+}
+
+WgBatchOf<1> single(const WgBatch& b) { return {1, b.total_tiles, {0}, {b.p[0]}}; }
+
 template <int kT>
 void launch_tiled(const WgBatch& batch, int acc, hipStream_t s) {
   const WgBatch b = tiled<kT>(batch, acc);
-  if (acc && rows_pay(b))
-    hipLaunchKernelGGL((k5_wgrad<true, kT, true>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads),
-                       0, s, b);
-  else if (acc)
-    hipLaunchKernelGGL((k5_wgrad<true, kT>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0, s,
-                       b);
-  else
-    hipLaunchKernelGGL((k5_wgrad<false, kT>), dim3(unsigned(b.total_tiles)), dim3(kWgThreads), 0,
-                       s, b);
+  const bool rows = acc && rows_pay(b);
+  if (b.num == 1) launch_tiled<kT>(single(b), acc, rows, s);
+  else launch_tiled<kT>(b, acc, rows, s);
+}
+
+template <int kMost>
+void launch_sums(const WgBatchOf<kMost>& b, hipStream_t s) {
+  hipLaunchKernelGGL(k5_tile_sums<kMost>, dim3(unsigned(b.total_tiles)), dim3(kSumsThreads), 0, s,
+                     b);
 }
 
 // The tile edge for one launch.  A 256 tile does the most work per LDS byte
@@ -655,7 +678,8 @@ hipError_t launch_wgrad(const WgBatch& batch, hipStream_t s) {
     } else {
       if (t == 128) launch_tiled<128>(batch, acc, s);
       else launch_tiled<64>(batch, acc, s);
-      hipLaunchKernelGGL(k5_tile_sums, dim3(unsigned(b.total_tiles)), dim3(kSumsThreads), 0, s, b);
+      if (b.num == 1) launch_sums(single(b), s);
+      else launch_sums(b, s);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
