@@ -40,6 +40,7 @@
 // 93 us in 256 tiles (two launches of at most 16 problems), 26 us in 208 tiles
 // of 128 (one launch of at most 32, 21 us, and the sums, 5 us).
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gnmr_internal.h"
@@ -635,32 +636,47 @@ void launch_sums(const WgBatchOf<kMost>& b, hipStream_t s) {
 }
 
 // The tile edge for one launch.  A 256 tile does the most work per LDS byte
-// and writes its own sum, but takes 7.5 us plus 1.0 us per K step of 64
+// and writes its own sum, but takes 6.4 us plus 1.0 us per K step of 64
 // however few of the 256 CUs have one; the smaller tiles add the k5_tile_sums
 // launch (about 5 us) and spread the same steps over 4 or 16 times the
-// workgroups.  Measured on square problems, call to call, 256 / 128 / 64 tile:
-//   tokens 4096:  G = 1: 71 / 37 / 24 us    G = 16: 72 / 38 / 26
-//                 G = 25: 72 / 38 / 37      G = 36: 72 / 39 / 47
-//                 G = 64: 73 / 46 / 63      G = 121: 74 / 77 / 118
-//                 G = 144: 77 / 101 / 135   (G: number of 256 tiles)
-//   tokens 1024:  G = 1: 23 / 16 / 13       G = 25: 24 / 18 / 17
-//                 G = 64: 25 / 21 / 24      G = 100: 26 / 26 / 35
-//   tokens 256:   G = 16: 11.9 / 12.9 / 11.2  G = 25: 12.3 / 13.2 / 13.0
-//                 G = 64: 13 / 15 / 17
-// So: the 64 tile while every CU gets at most one and there are 4 steps to
-// share, or at most two and 16 steps; the 128 tile while every CU gets at most
-// one and the steps outweigh the second launch (4 plus one per 64 tiles more),
-// or at most two and 32 steps; otherwise the 256 tile.
+// workgroups.  Measured on square problems, call to call, 256 / 128 / 64 tile, us
+// (G: number of 256 tiles):
+//   tokens      256              512              1024             2048             4096
+//   G = 1       10.7  9.3  7.9   14.7 11.0  8.9   22.5 14.6 10.8   38.2 21.6 14.8   70  35  23
+//   G = 16      11.1 10.3  8.6   15.1 12.1  9.7   22.9 15.6 11.7   38.7 22.6 16.0   71  37  26
+//   G = 25      11.3 11.0 10.7   15.2 12.7 12.4   23.3 16.4 15.8   39.1 23.3 22.4   71  38  36
+//   G = 36      11.4 11.9 12.3   15.4 13.8 14.7   23.4 17.5 19.8   39.5 24.1 28.1   71  39  47
+//   G = 64      12.0 13.9 15.7   16.0 15.8 18.3   24.2 20.0 22.8   40.1 26.8 36.1   72  45  67
+//   G = 81      12.3 16.7 18.2   16.4 19.8 21.4   24.5 24.0 28.8   40.4 37.1 48.0   72  64  86
+//   G = 100     12.9 17.6 20.3   17.1 20.2 23.8   25.2 24.8 33.3   41.4 39.0 57.1   73  68 107
+//   G = 121     13.1 19.2 21.5   17.3 21.2 25.8   25.5 26.3 37.1   41.2 41.8 61.8   74  73 116
+//   G = 144     13.5 21.4 22.7   17.7 24.5 28.1   25.9 33.4 40.6   42.2 54.6 68.2   76  99 126
+// and at 8,192 tokens G = 81: 139 / 120, G = 100: 138 / 126, G = 121: 151 / 141,
+// G = 144: 145 / 186.  So: the 64 tile while every CU gets at most one and there are
+// 4 steps to share, or at most two and 16 steps; the 128 tile while every CU gets at
+// most one and the steps outweigh the second launch (4 plus one per 64 tiles more),
+// or at most two and 32 steps; otherwise the 256 tile.  Two of the smaller tiles to a
+// CU do not pay where the problems are no higher or wider than one: the larger tile
+// then has as many, one to a CU.  64 x 32768 of 2,048, 4,096 and 8,192 tokens in 128
+// and 64 tiles: 28.2 and 29.4, 46.6 and 52.4, 96 and 118 us; 128 x 38400 in 256 and 128
+// tiles: 41.2 and 42.1, 90 and 98, 176 and 189.  (With a 256 tile on most CUs the chip's
+// power evens that out: 128 x 65536 57.3 and 56.5, 111 and 116, accumulating 63.2 and
+// 59.4, 119 and 120.)
 int tile_edge(const WgBatch& batch, int acc) {
-  const WgBatch b = tiled<64>(batch, acc);
-  const int64_t n64 = b.total_tiles, n128 = tiled<128>(batch, acc).total_tiles;
-  int64_t steps = 0;
-  for (int i = 0; i < b.num; ++i)
-    steps = b.p[i].K > steps * kWgBK ? (b.p[i].K + kWgBK - 1) / kWgBK : steps;
+  int64_t n64 = 0, n128 = 0, n256 = 0, steps = 0;
+  for (int i = 0; i < batch.num; ++i) {
+    const WgProblem& p = batch.p[i];
+    if (p.accumulate != acc) continue;
+    const auto tiles = [&p](int t) { return int64_t((p.M + t - 1) / t) * ((p.N + t - 1) / t); };
+    n64 += tiles(64);
+    n128 += tiles(128);
+    n256 += tiles(256);
+    steps = std::max(steps, (p.K + kWgBK - 1) / kWgBK);
+  }
   if (n64 <= 256 && steps >= 4) return 64;
-  if (n64 <= 512 && steps >= 16) return 64;
+  if (n64 <= 512 && steps >= 16 && n64 > 2 * n128) return 64;
   if (n128 <= 256 && steps >= 4 + n128 / 64) return 128;
-  if (n128 <= 512 && steps >= 32) return 128;
+  if (n128 <= 512 && steps >= 32 && (n128 > 2 * n256 || n256 > 192)) return 128;
   return 256;
 }
 

@@ -104,3 +104,23 @@ def test_more_problems_than_one_launch_holds():
         assert np.array_equal(dw, want), f"problem {i}"
         np.testing.assert_allclose(ss, W.tile_sumsq(want), rtol=SS_RTOL, atol=0,
                                    err_msg=f"problem {i}")
+
+
+# Around the limits at which the tile of one problem changes: 256 and 512 tiles of 64
+# and of 128, steps that do and do not pay, problems no higher or wider than a tile.
+# The 256 tile beside a filler gives the same bits.
+@pytest.mark.parametrize("M,N,T", [
+    (1024, 1024, 255), (1024, 1032, 256), (1408, 1472, 1023), (1408, 1472, 960),
+    (64, 16392, 1024), (72, 16392, 1024), (2048, 2048, 448), (2048, 2048, 449),
+    (2056, 2048, 1984), (2816, 2816, 1985), (128, 38400, 2048), (128, 50000, 2048),
+    (136, 32776, 2048), (38400, 8, 2048)])
+def test_one_problem_where_its_tile_changes(M, N, T):
+    torch = require_gpu()
+    print(f"wgrad tile rule M={M} N={N} T={T}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N + T)
+    bits = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16().view(
+        torch.int16).cpu().numpy()
+    dy, x = bits(T, M), bits(T, N)
+    (dw, ss), = launch(torch, [(dy, x, np.zeros((M, N), np.int16), 0)], 0)
+    (want, ss_want), = launch(torch, [(dy, x, np.zeros((M, N), np.int16), 0)], 5888)
+    assert np.array_equal(dw, want) and np.array_equal(ss, ss_want)
