@@ -377,25 +377,26 @@ namespace {
 // widths, a launch each and one, 7.4 and 4.7 us (5120 and 13824 features, 0.9 MB),
 // 8.3 and 5.6 (3.9 MB), 24.3 and 21.6 (63 MB), twelve widths 41 and 4.9 (0.9 MB),
 // 62 and 24.6 (63 MB).  (A workgroup of 256 lanes with eight vectors each for every
-// row: 5.0, 5.6 and 28.0 of the first three.)  Past that, rows of up to 1,024 features
-// want eight waves and lose about 0.05 us a MB, against 2 us for each further launch:
-// 28 inputs of 1024 and 2816, a launch each and one, 31.2 and 32.9 us (49 MB of the
-// narrow), 74 and 83 (170 MB); 256, 512 and 4096 62.6 and 60.7 (100 MB); 2048 and 5504
-// 38.7 and 36.2 (none, 100 MB in all); twelve widths 73.8 and 41.8 (33 MB), 186 and 149
-// (133 MB).  A large table's launches are long beside what they cost: 4096 and 11008 at
-// 500 MB 162 and 165, 1 GB 322 and 323.
-constexpr int64_t kMixedBytes = int64_t(384) << 20, kMixedNarrow = int64_t(32) << 20;
+// row: 5.0, 5.6 and 28.0 of the first three.)  Past that, rows of two vectors a lane,
+// or three in a wavefront, want eight waves and lose about 0.03 to 0.05 us a MB, against
+// 2 us for each further launch.  With none of them one launch: 2048 and 5504 at 100 MB
+// 38.7 and 36.2, 12288 and 16384 at 68 MB 29.5 and 26.7.  With many a launch each: 1064
+// and 3104 at 250 MB 101 and 108, 1112 and 3032 at 94 MB 42.0 and 43.6 (64 MB of them).
+// Twelve widths, half of them such: 73.8 and 41.8 at 100 MB, 186 and 149 at 400.  A
+// large table's launches are long beside what they cost: 4096 and 11008 at 500 MB 162
+// and 165, 1 GB 322 and 323.
+constexpr int64_t kMixedBytes = int64_t(384) << 20, kMixedFew = int64_t(32) << 20;
 bool one_launch(const int64_t* class_off, int64_t bytes) {
   int present = 0;
-  int64_t narrow = 0;  // at most these bytes are of rows up to 1,024 features
+  int64_t few = 0;  // at most these bytes are of rows that want eight waves
   for (int c = 0; c < kK4Classes; ++c) {
     const int64_t rows = class_off[c + 1] - class_off[c];
-    const int widest = kClasses[c].lanes * kClasses[c].vpt * 8;
+    const int lanes = kClasses[c].lanes, vpt = kClasses[c].vpt;
     present += rows > 0 ? 1 : 0;
-    if (widest <= 1024) narrow += rows * widest * 2;
+    if (vpt == 2 || (vpt == 3 && lanes == 64)) few += rows * lanes * vpt * 16;
   }
   if (present < 2 || bytes > kMixedBytes) return false;
-  return bytes <= kK4CachedBytes || narrow <= kMixedNarrow * (present - 1);
+  return bytes <= kK4CachedBytes || few <= kMixedFew * (present - 1);
 }
 
 template <bool kCached>

@@ -126,10 +126,11 @@ def test_classes_of_a_small_table_in_one_launch(rows, widths, past):
 
 
 # a launch per class: past 384 MB, and past 64 MB where more than 32 MB for each
-# class but one are rows of up to 1,024 features; below either, one launch
+# class but one are rows of two vectors a lane; below either, one launch
 @pytest.mark.parametrize("widths,filler,rows", [
     (tuple(WIDTHS), 16384, 12500), (tuple(WIDTHS), 16384, 11500),
-    ((2312,), 1024, 34000), ((1000, 8192, 12296), 512, 100000), ((1000, 8192, 12296), 512, 70000)])
+    ((2312,), 1024, 34000), ((1000, 8192, 12296), 512, 100000), ((1000, 8192, 12296), 512, 70000),
+    ((6144,), 2048, 17000)])
 def test_classes_of_a_large_table(widths, filler, rows):
     torch = require_gpu()
     from paper_2606_00539_amd import Actuator
