@@ -146,8 +146,9 @@ hipError_t launch_unit_sumsq(const int64_t* unit_item_off, const float* partial,
                              int64_t num_items, int32_t num_units, double* out, hipStream_t s);
 hipError_t launch_update(const UpdateArgs& a, int64_t num_items, SelectArgs* sel, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
-// K2 and K3 as one single-workgroup launch: used when the workload is small (at
-// most 1024 units, and norms given or partials that fit in LDS).
+// K2 and K3 as one single-workgroup launch: used when the workload is small (norms
+// given, or up to 10,240 partials: at most 1,024 units, 32 where a wavefront sums a
+// unit's partials and 8 where a workgroup's worth of lanes does).
 bool single_launch_update_select(const UpdateArgs& a, int64_t num_items);
 hipError_t launch_update_select(const UpdateArgs& u, const SelectArgs& s, int64_t num_items,
                                 hipStream_t st);
