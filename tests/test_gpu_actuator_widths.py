@@ -155,3 +155,23 @@ def test_classes_of_a_large_table(widths, filler, rows):
         assert np.array_equal(o.cpu().numpy().view(np.uint16).reshape(w.shape), w), w.shape
     got = fill[rows - 1].cpu().numpy().view(np.uint16)[None]
     assert np.array_equal(got, FQ.fakequant_rows(last, LOW)) and not fill[:-1].any()
+
+
+@pytest.mark.parametrize("cols", WIDTHS)
+def test_a_table_of_one_width(cols):
+    """A table of one class takes that class's own kernel."""
+    torch = require_gpu()
+    from paper_2606_00539_amd import Actuator
+
+    print(f"actuator table of one width {cols}", flush=True)
+    rng = np.random.default_rng(cols)
+    acts = [rows_of(rng, r, cols) for r in (1, 3, 33)]
+    mask = np.array([0, 1, 0], np.uint8)
+    d_in = [to_device(torch, a) for a in acts]
+    d_out = [torch.full_like(t, 0x5555) for t in d_in]
+    segs = [(i, o, a.shape[0], cols, b) for b, (i, o, a) in enumerate(zip(d_in, d_out, acts))]
+    with Actuator(segs, 3) as act:
+        act.apply(torch.from_numpy(mask).to("cuda"), LOW, 3)
+        torch.cuda.synchronize()
+    for o, w in zip(d_out, FQ.actuate(acts, mask, LOW, 3)):
+        assert np.array_equal(o.cpu().numpy().view(np.uint16).reshape(w.shape), w)
