@@ -303,7 +303,8 @@ gnmr_status gnmr_info(const gnmr_ctx* ctx, int64_t* num_items, int64_t* item_byt
  * the recovery path chosen by the controller (Alg. 2: "use the recovery path
  * for b" / "use the low-cost path").  Both paths are per-token fake
  * quantisation (App. E.2 quantisation-simulated operators; Sec. 5.1 and App.
- * E.4: token-wise low-bit saved activations; Sec. 5.3 and App. E.3: INT8): every token (row) is scaled into
+ * E.4: token-wise low-bit saved activations; Sec. 5.3 and App. E.3: INT8):
+ * every token (row) is scaled into
  * the format's representable range by its largest magnitude, rounded to the
  * nearest representable value (ties to the even significand or integer,
  * saturating) and rescaled, in fp32: inv = fmax / amax, s = amax / fmax, y = x * inv,
@@ -339,9 +340,9 @@ typedef struct gnmr_actuator gnmr_actuator;
  * may free it).  num_units bounds the unit indices.  Allocates device memory
  * for the tables (8 B per row, 24 B per segment).  At most 67,108,860 rows of
  * up to 4096 features and 16,777,215 longer rows in all; GNMR_E_INVALID
- * beyond.  A call launches one kernel per class of row widths present (at most
- * 12), or, with up to 64 MB of input, one for all rows of up to 8192 features
- * and one per wider class. */
+ * beyond.  A call launches one kernel for all rows with up to 64 MB of input, and
+ * up to 384 MB where that is the faster way; otherwise one kernel per class of
+ * row widths present (at most 12). */
 gnmr_status gnmr_actuator_create(gnmr_actuator** out, const gnmr_act_segment* segs,
                                  int64_t num_segments, int32_t num_units, void* stream);
 
@@ -362,8 +363,8 @@ gnmr_status gnmr_actuate(gnmr_actuator* act, const uint8_t* d_mask, int32_t fmt_
  * fmt_recovery when d_mask[unit] != 0, else fmt_low (d_mask: device bytes,
  * e.g. the controller's mask from gnmr_device_outputs, read when the kernel
  * runs).  Allocates nothing and launches one kernel (none when rows = 0, more
- * where one launch's grid cannot hold the rows); asynchronous on `stream`.  GNMR_E_INVALID on a bad argument, GNMR_E_HIP on
- * a launch failure. */
+ * where one launch's grid cannot hold the rows); asynchronous on `stream`.
+ * GNMR_E_INVALID on a bad argument, GNMR_E_HIP on a launch failure. */
 gnmr_status gnmr_actuate_matrix(const void* in, void* out, int64_t rows, int32_t cols,
                                 const uint8_t* d_mask, int32_t unit, int32_t fmt_low,
                                 int32_t fmt_recovery, void* stream);
